@@ -63,8 +63,9 @@ __device__ __forceinline__ int view_of_group(const sr_camera* __restrict__ cams,
 constexpr uint32_t kInstIdMask = (1u << SR_INST_ID_BITS) - 1u;
 __device__ __forceinline__ bool inst_covers(uint32_t v, int sx, int sy) {
     const uint32_t sub = v >> SR_INST_ID_BITS;
-    return (int)(sub & 3u) <= sx && sx <= (int)((sub >> 2) & 3u) && (int)((sub >> 4) & 3u) <= sy &&
-           sy <= (int)((sub >> 6) & 3u);
+    // no short circuit: four compares, no branches
+    return ((int)(sub & 3u) <= sx) & (sx <= (int)((sub >> 2) & 3u)) & ((int)((sub >> 4) & 3u) <= sy) &
+           (sy <= (int)((sub >> 6) & 3u));
 }
 
 // ---------------------------------------------------------------------------
@@ -74,62 +75,6 @@ __device__ __forceinline__ bool inst_covers(uint32_t v, int sx, int sy) {
 template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_f(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
-}
-
-// Wave-wide sums of N per-lane values (N = 8 or 16) by transposition: at
-// every step the values of two registers are exchanged between the two halves
-// of the lanes being combined, so each step halves both the number of
-// registers and the number of lanes that share a value.  Halves of the wave
-// (lanes l, l^32) and pairs of rows (l, l^16) are combined with the gfx950
-// permlane swaps, lanes l, l^1 and l, l^2 with DPP quad permutations, the
-// remaining lanes l, l^4, l^8 with row rotations.  On return every lane holds
-// the wave total of component wave_tsum_comp<N>(lane).
-template <int N>
-__device__ __forceinline__ int wave_tsum_comp(int lane) {
-    const int r = lane >> 4;
-    const int pr = ((r & 1) << 1) | (r >> 1);   // row 0,1,2,3 -> 0,2,1,3
-    const int p = lane & 1;
-    if (N == 16) return 8 * ((lane >> 1) & 1) + 4 * p + pr;
-    return 4 * p + pr;
-}
-
-template <int N>
-__device__ __forceinline__ float wave_tsum(const float* v) {
-    static_assert(N == 8 || N == 16, "8 or 16 components");
-    float s[N / 2];
-#pragma unroll
-    for (int j = 0; j < N / 2; ++j) {
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[2 * j]), __float_as_uint(v[2 * j + 1]),
-                                                        false, false);
-        s[j] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    float t[N / 4];
-#pragma unroll
-    for (int m = 0; m < N / 4; ++m) {
-        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[2 * m]), __float_as_uint(s[2 * m + 1]),
-                                                        false, false);
-        t[m] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    }
-    const bool odd = (__lane_id() & 1) != 0;
-    float u[N / 8];
-#pragma unroll
-    for (int n = 0; n < N / 8; ++n) {
-        const float keep = odd ? t[2 * n + 1] : t[2 * n];
-        const float send = odd ? t[2 * n] : t[2 * n + 1];
-        u[n] = keep + dpp_f<0xB1, 0xF>(send);   // quad_perm [1,0,3,2]
-    }
-    float w;
-    if (N == 16) {
-        const bool b1 = (__lane_id() & 2) != 0;
-        const float keep = b1 ? u[1] : u[0];
-        const float send = b1 ? u[0] : u[1];
-        w = keep + dpp_f<0x4E, 0xF>(send);      // quad_perm [2,3,0,1]
-    } else {
-        w = u[0] + dpp_f<0x4E, 0xF>(u[0]);
-    }
-    w += dpp_f<0x124, 0xF>(w);                  // row_ror:4
-    w += dpp_f<0x128, 0xF>(w);                  // row_ror:8
-    return w;
 }
 
 template <int CTRL>
@@ -157,6 +102,9 @@ __device__ __forceinline__ uint32_t wave_max2_bits(float a, float b) {
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
+// old with lane `lane` (uniform) replaced by v (uniform).
+__device__ int lane_write(int v, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
 // ---------------------------------------------------------------------------
 // Evaluation of one (pixel, surfel) pair.  Shared verbatim by the forward,
 // backward and pruning kernels so that they take identical decisions: every
@@ -172,30 +120,54 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 // ---------------------------------------------------------------------------
 struct PairEval {
     float dx, dy, w0, w1, w2, rho_f;
-    bool pass, s_ok;
+    bool q_ok, w_ok, f_ok, s_ok;
     float r, u, v, rho, G, a, z;   // r = 1/w2
     bool surf, clamped;
 };
 
+// A geometry record as the evaluation reads it.
+struct SurfelGeom {
+    float A0, A1, A2, B0, B1, B2, C0, C1, C2, cx, cy, o, m30, m31, m32, L, L2;   // L2 = 2 L
+};
+
+// a b + c.  With a in a scalar register (SCALAR) the result takes a register
+// of its own: the compiler would accumulate into c's, which the next record's
+// load takes, and copy it out.
+template <bool SCALAR>
+__device__ __forceinline__ float fma_rec(float a, float b, float c) {
+    if (!SCALAR) return __builtin_fmaf(a, b, c);
+    float d;
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "s"(a), "v"(b), "v"(c));
+    return d;
+}
+
 // Stage 1: the cutoff test (no division, no exponential).
-__device__ __forceinline__ void eval_test(const float4& g0, const float4& g1, const float4& g2,
-                                          const float4& g3, float px, float py, PairEval& e) {
+template <bool SCALAR>
+__device__ __forceinline__ void eval_test(const SurfelGeom& s, float px, float py, PairEval& e) {
 #pragma clang fp contract(off)
-    e.dx = px - g2.y;
-    e.dy = py - g2.z;
-    e.w0 = __builtin_fmaf(g0.x, e.dx, __builtin_fmaf(g0.w, e.dy, g1.z));
-    e.w1 = __builtin_fmaf(g0.y, e.dx, __builtin_fmaf(g1.x, e.dy, g1.w));
-    e.w2 = __builtin_fmaf(g0.z, e.dx, __builtin_fmaf(g1.y, e.dy, g2.x));
-    const float L = g3.w;
+    e.dx = px - s.cx;
+    e.dy = py - s.cy;
+    e.w0 = __builtin_fmaf(s.A0, e.dx, fma_rec<SCALAR>(s.B0, e.dy, s.C0));
+    e.w1 = __builtin_fmaf(s.A1, e.dx, fma_rec<SCALAR>(s.B1, e.dy, s.C1));
+    e.w2 = __builtin_fmaf(s.A2, e.dx, fma_rec<SCALAR>(s.B2, e.dy, s.C2));
     e.rho_f = __builtin_fmaf(e.dx, e.dx, e.dy * e.dy);
     const float q = __builtin_fmaf(e.w0, e.w0, e.w1 * e.w1);
     const float w22 = e.w2 * e.w2;
-    e.s_ok = (q <= (2.0f * L) * w22) && (e.w2 != 0.0f);
-    e.pass = e.s_ok || (e.rho_f <= L);
+    e.q_ok = q <= s.L2 * w22;
+    e.w_ok = e.w2 != 0.0f;
+    e.s_ok = e.q_ok && e.w_ok;
+    e.f_ok = e.rho_f <= s.L;
 }
 
+// The lanes whose pair passes the cutoff, and a lane's own bit of a mask (no
+// vector instruction: the mask itself is the condition).
+__device__ __forceinline__ uint64_t pass_mask(const PairEval& e) {
+    return (ballot64(e.q_ok) & ballot64(e.w_ok)) | ballot64(e.f_ok);
+}
+__device__ __forceinline__ bool in_mask(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 // Stage 2: intersection, Gaussian value, alpha and depth of a passing pair.
-__device__ __forceinline__ void eval_finish(const float4& g2, const float4& g3, float alpha_max, PairEval& e) {
+__device__ __forceinline__ void eval_finish(const SurfelGeom& s, float alpha_max, PairEval& e) {
 #pragma clang fp contract(off)
     e.r = __builtin_amdgcn_rcpf(e.w2);
     e.u = e.w0 * e.r;
@@ -205,12 +177,12 @@ __device__ __forceinline__ void eval_finish(const float4& g2, const float4& g3, 
     e.rho = e.surf ? rho_s : e.rho_f;
     // exp(-rho) = 2^(-rho log2 e)
     e.G = __builtin_amdgcn_exp2f(-1.4426950408889634f * e.rho);
-    const float oG = g2.w * e.G;
+    const float oG = s.o * e.G;
     e.clamped = oG > alpha_max;
     // min(oG, alpha_max) as the median of (oG, 0, alpha_max): oG >= 0, and
     // one instruction where the select needs the bound in a vector register
     e.a = __builtin_amdgcn_fmed3f(oG, 0.0f, alpha_max);
-    e.z = e.surf ? __builtin_fmaf(g3.x, e.u, __builtin_fmaf(g3.y, e.v, g3.z)) : g3.z;
+    e.z = e.surf ? __builtin_fmaf(s.m30, e.u, __builtin_fmaf(s.m31, e.v, s.m32)) : s.m32;
 }
 
 // Per-pixel terms of the masked losses (Eq. 1 and the L1 part of Eq. 2) and

@@ -9,8 +9,9 @@
 // depth, normal and distortion.
 //
 // One workgroup per (view, tile) over all views of the batch in a single
-// launch; one thread per pixel; surfel records are staged in LDS one batch
-// per workgroup-size entries; every pair is evaluated with the shared
+// launch; one thread per pixel; the entries of a tile are gathered in batches
+// in LDS, their records read per wave from LDS or through the scalar cache
+// (EntryRec); every pair is evaluated with the shared
 // eval_test()/eval_finish() so that forward, backward and pruning take identical
 // decisions.
 #include <mutex>
@@ -50,7 +51,8 @@ struct TileCtx {
     int sx, sy;      // tile coordinates inside its binning group
     bool inside;
     int64_t pix_off;
-    uint32_t start, n;
+    uint32_t start;
+    int n;           // runs hold at most one entry per surfel of the view: below 2^SR_INST_ID_BITS
     float bg[3];
 };
 
@@ -89,15 +91,23 @@ __device__ __forceinline__ void tile_ctx(const sr_camera* __restrict__ cams, int
     t.bg[0] = c.bg[0]; t.bg[1] = c.bg[1]; t.bg[2] = c.bg[2];
     const uint2 rg = ranges[tile];
     t.start = rg.x;
-    t.n = idle ? 0u : rg.y - rg.x;
+    t.n = idle ? 0 : (int)(rg.y - rg.x);
 }
 
 constexpr int kMaxWaves = 8;    // waves per workgroup (tiles of up to 512 pixels)
 
-// Five waves per SIMD: the register budget (at most 96 VGPRs, no spills)
-// that keeps the compositing kernels issue-bound; the compiler would
-// otherwise spend up to 104 registers and drop to four.
-#define SR_RASTER_OCCUPANCY __attribute__((amdgpu_waves_per_eu(5)))
+// Waves per SIMD the kernels are compiled for (the register budget: 96 VGPRs
+// at five, 80 at six, 72 at seven).  The walks themselves fit all three; the
+// float64 culling bounds of the staging spill a few registers below 96, once
+// per staged entry.  Measured with scalar records (compositing kernel; 1M
+// surfels x 16 views / 3M x 8 / one 800x800 view of 100k): training step 6.64 /
+// 5.47 / 0.372 ms at five, 6.13 / 5.13 / 0.369 at six, 5.93 / 4.97 / 0.381 at
+// seven; forward of four 1559x1039 views 1.07 / 1.00 / 1.02 ms at five to
+// seven; backward with the depth terms 2.33 / 2.29 ms there but 0.42 / 0.45 on
+// one 800x600 view; the pruning pass of 100 views 50.5 / 50.5 / 49.7 ms.  With
+// records in LDS (few tiles) four and five measure the same.
+#define SR_OCCUPANCY(waves) __attribute__((amdgpu_waves_per_eu(waves)))
+constexpr int kFwdWaves = 6, kPruneWaves = 7, kBwdWaves = 5, kTrainWaves = 6, kLdsWaves = 5;
 
 // MODE bits: 1 shade (colour, depth, normal, distortion outputs), 2 occlusion
 // statistics, 4 count reached/blended pairs (work accounting), 8 median depth
@@ -132,12 +142,12 @@ constexpr int kShade = 1, kStats = 2, kCount = 4, kMedian = 8, kRect = 16, kHits
 // and backward skip the same entries.
 template <int TW, int NW>
 __device__ __forceinline__ uint32_t wave_bits(const float4& g0, const float4& g1, const float4& g2, float Lf,
-                                              const float4& a1, int tx0, int ty0) {
+                                              uint2 rr, int tx0, int ty0) {
     constexpr int WB = kWaveBlock;
     static_assert(TW % WB == 0 && NW % (TW / WB) == 0, "waves cover whole 8x8 blocks of the tile");
     constexpr int BX = TW / WB, BY = NW / BX;     // blocks per tile row and column
     constexpr double tau = 1e-3, mg = 1e-3;
-    const uint32_t rx = __float_as_uint(a1.z), ry = __float_as_uint(a1.w);
+    const uint32_t rx = rr.x, ry = rr.y;     // x_lo | x_hi << 16, y_lo | y_hi << 16
     const int ilo = (int)(rx & 0xffffu), ihi = (int)(rx >> 16), jlo = (int)(ry & 0xffffu), jhi = (int)(ry >> 16);
     const double cx = g2.y, cy = g2.z, L = Lf;
     // the conic's coefficients, independent of the columns
@@ -211,26 +221,100 @@ __device__ __forceinline__ uint32_t wave_bits(const float4& g0, const float4& g1
     return bits;
 }
 
-// Mask of the entries of run c (of 64) whose wave bit (kept in the last slot
-// of the staged appearance record) is set for this wave.
-__device__ __forceinline__ uint64_t wave_live_mask(const float4* __restrict__ a1, int c, int cnt) {
-    const int k = c * 64 + __lane_id();
-    const int w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x) >> 6;
-    return ballot64(k < cnt && ((__float_as_uint(a1[k].w) >> w) & 1u));
+// A staged entry's record, read by the whole wave (the wave's entry is
+// uniform), from one of two places:
+//
+// SCALAR: through the scalar cache into scalar registers, 18 to 24 words in
+//   two or three loads, fetched one entry ahead.  Read as broadcasts from LDS
+//   (six 16-byte reads) the records kept the LDS unit busy for two thirds of
+//   the kernel's time.  A vector instruction takes one scalar operand, so the
+//   addends C, which meet a second one, come from LDS (staged in c, with
+//   twice the cutoff in the fourth slot).
+// else: broadcasts from LDS.  Where few tiles leave every SIMD a wave or two,
+//   nothing hides a scalar load that misses its cache, and a wave's own
+//   latency per entry is the kernel's time; the LDS unit is then idle.
+//
+// The rule is on the number of tiles (scalar_records).
+typedef float F16v __attribute__((ext_vector_type(16)));
+typedef float F4v __attribute__((ext_vector_type(4)));
+typedef float F2v __attribute__((ext_vector_type(2)));
+template <typename T>
+using ConstMem = const T __attribute__((address_space(4)));
+
+template <bool SCALAR, int NB, bool APP>
+struct RecStage;
+template <int NB, bool APP>
+struct RecStage<true, NB, APP> {
+    float4 c[NB];                 // C0, C1, C2, 2 L
+    __device__ __forceinline__ void put(int k, const float4 (&g)[kGeomF4], const float4*) {
+        c[k] = make_float4(g[1].z, g[1].w, g[2].x, 2.0f * g[3].w);
+    }
+};
+template <int NB, bool APP>
+struct RecStage<false, NB, APP> {
+    float4 g[kGeomF4][NB];
+    float4 a[APP ? kAppF4 : 1][APP ? NB : 1];
+    __device__ __forceinline__ void put(int k, const float4 (&gq)[kGeomF4], const float4* app) {
+#pragma unroll
+        for (int q = 0; q < kGeomF4; ++q) g[q][k] = gq[q];
+        if (APP) {
+            a[0][k] = app[0];
+            a[1][k] = app[1];
+        }
+    }
+};
+
+struct EntryRec {
+    F16v g;
+    F4v a0;     // colour, normal x
+    F2v a1;     // normal y, z
+    float4 c;   // SCALAR: C0, C1, C2, 2 L
+};
+
+// geom_v, app_v: the view's records; g: uniform surfel id.
+template <bool APP, bool NORMAL>
+__device__ __forceinline__ void load_scalar(const float4* __restrict__ geom_v, const float4* __restrict__ app_v,
+                                            uint32_t g, EntryRec& r) {
+    r.g = *(ConstMem<F16v>*)(uintptr_t)((const char*)geom_v + (size_t)(g * (uint32_t)(16 * kGeomF4)));
+    if (APP) {
+        const char* a = (const char*)app_v + (size_t)(g * (uint32_t)(16 * kAppF4));
+        r.a0 = *(ConstMem<F4v>*)(uintptr_t)a;
+        if (NORMAL) r.a1 = *(ConstMem<F2v>*)(uintptr_t)(a + 16);
+    }
 }
 
-// The same for the slots [lo, hi), keeping only run positions below maxpos.
-__device__ __forceinline__ uint64_t wave_live_mask_from(const float4* __restrict__ a1, int c, int lo, int hi,
-                                                        uint32_t maxpos) {
-    const int k = c * 64 + __lane_id();
-    const int w = (int)__builtin_amdgcn_readfirstlane(threadIdx.x) >> 6;
-    bool live = k >= lo && k < hi;
-    if (live) {
-        const float4 r = a1[k];
-        live = ((__float_as_uint(r.w) >> w) & 1u) && __float_as_uint(r.z) < maxpos;
+template <bool APP, typename Stage>
+__device__ __forceinline__ void load_lds(const Stage& st, int k, EntryRec& r) {
+#pragma unroll
+    for (int q = 0; q < kGeomF4; ++q) {
+        const float4 v = st.g[q][k];
+        r.g[4 * q] = v.x;
+        r.g[4 * q + 1] = v.y;
+        r.g[4 * q + 2] = v.z;
+        r.g[4 * q + 3] = v.w;
     }
-    return ballot64(live);
+    if (APP) {
+        const float4 a0 = st.a[0][k];
+        const float2 a1 = *reinterpret_cast<const float2*>(&st.a[1][k]);
+        r.a0 = F4v{a0.x, a0.y, a0.z, a0.w};
+        r.a1 = F2v{a1.x, a1.y};
+    }
 }
+
+template <bool SCALAR>
+__device__ __forceinline__ SurfelGeom geom_of(const EntryRec& r) {
+    return SurfelGeom{r.g[0],  r.g[1],  r.g[2],  r.g[3],  r.g[4],  r.g[5],
+                      SCALAR ? r.c.x : r.g[6], SCALAR ? r.c.y : r.g[7], SCALAR ? r.c.z : r.g[8],
+                      r.g[9],  r.g[10], r.g[11], r.g[12], r.g[13], r.g[14], r.g[15],
+                      SCALAR ? r.c.w : 2.0f * r.g[15]};
+}
+
+// Staged entries: the surfel id with the wave bits above it (ids hold
+// SR_INST_ID_BITS bits), and the run position.
+static_assert(SR_INST_ID_BITS + 4 <= 32, "wave bits above the surfel id");
+
+// This wave's index in its workgroup.
+__device__ __forceinline__ int wave_index() { return (int)__builtin_amdgcn_readfirstlane(threadIdx.x) >> 6; }
 
 // Wave bits of the staged entries kept from the forward to the backward of
 // the fused step (LDS, 4 bits per run position, 16 bytes per thread of the
@@ -255,28 +339,34 @@ struct PixFwd {
     uint32_t last, kmed;
 };
 
-// LDS staging of the forward: NT records per batch.
-template <int NT, int MODE>
+// LDS staging of the forward: NT entries per batch.
+template <int NT, int MODE, bool SCALAR>
 struct FwdSmem {
-    float4 g[kGeomF4][NT];
-    // appearance (shading) in a[0], a[1].xy; the run position of the entry in
-    // a[1].z and the wave bits in a[1].w in every mode
-    float4 a[kAppF4][NT];
-    uint32_t id[(MODE & (kStats | kHits)) ? NT : 1];
+    RecStage<SCALAR, NT, (MODE & kShade) != 0> rec;
+    uint32_t id[NT];          // surfel id | wave bits << SR_INST_ID_BITS
+    uint32_t pos[NT];         // list index: run position + 1
     // occlusion statistics of the batch's entries over the workgroup's waves
     // (hits, then with kStats the max alpha and max weight bits), added to
     // the global ones once per (tile, entry) at the end of the batch
     uint32_t st[(MODE & kStats) ? 3 : 1][(MODE & (kStats | kHits)) ? NT : 1];
     uint32_t wcnt[NT / 64 + 1];   // gathering: members per wave, then the resume position
+    uint32_t alive[NT / 64];      // waves with a pixel that has not terminated
 };
 
-// LDS staging and per-record accumulators of the backward.
-template <int BATCH>
+// LDS staging and per-record accumulators of the backward.  acc[k] holds the
+// sums over the workgroup's pixels of entry k (wave_contract); the padding to an
+// odd stride keeps the per-thread reads of the flush free of bank conflicts.
+template <int NT, int BATCH, bool GEO, bool HITS, bool SCALAR>
 struct BwdSmem {
-    float4 g[kGeomF4][BATCH];
-    float4 a[kAppF4][BATCH];      // as in the forward: a[1].z run position, a[1].w wave bits
-    uint32_t rec[BATCH];
-    float acc[BATCH][kNumGrad];
+    static constexpr int kAcc = GEO ? 23 : 17;
+    RecStage<SCALAR, BATCH, true> rec;
+    float2 mid[BATCH];            // the tile's middle relative to the projected centre
+    uint32_t id[BATCH];           // surfel id | wave bits << SR_INST_ID_BITS
+    uint32_t pos[BATCH];          // run position
+    float4 xp[NT];                // transposition scratch, 64 slots per wave
+    float acc[BATCH][kAcc];
+    uint32_t hit[HITS ? BATCH : 1];
+    uint64_t touched[(BATCH + 63) / 64];     // entries some pixel of the tile blends
     uint32_t maxn;
     uint32_t wcnt[kMaxWaves + 1];
 };
@@ -291,12 +381,12 @@ struct BwdSmem {
 // member placed and reports where the next batch resumes.  Returns the
 // number of members placed in this round; block-uniform.
 template <int NT, bool ASC>
-__device__ __forceinline__ int gather_round(const TileCtx& t, const uint32_t* __restrict__ vals, int64_t pos,
-                                            int fill, int cap, float4* __restrict__ a0, float4* __restrict__ a1,
-                                            uint32_t* wcnt, int64_t& next) {
+__device__ __forceinline__ int gather_round(const TileCtx& t, const uint32_t* __restrict__ vals, int pos,
+                                            int fill, int cap, uint32_t* __restrict__ id, uint32_t* __restrict__ rpos,
+                                            uint32_t* wcnt, int& next) {
     const int tid = threadIdx.x, lane = __lane_id(), w = tid >> 6;
-    const int64_t j = ASC ? pos + tid : pos - NT + tid;
-    const bool in = ASC ? j < (int64_t)t.n : j >= 0;
+    const int j = ASC ? pos + tid : pos - NT + tid;
+    const bool in = ASC ? j < t.n : j >= 0;
     const uint32_t gv = in ? vals[t.start + (uint32_t)j] : 0u;
     const bool mem = in && inst_covers(gv, t.sx, t.sy);
     const uint64_t bm = ballot64(mem);
@@ -315,27 +405,29 @@ __device__ __forceinline__ int gather_round(const TileCtx& t, const uint32_t* __
     const int taken = fill + rank;
     if (mem && taken < cap) {
         const int slot = ASC ? taken : cap - 1 - taken;
-        a0[slot].x = __uint_as_float(gv);
-        a1[slot].z = __uint_as_float((uint32_t)j);
+        id[slot] = gv;
+        rpos[slot] = (uint32_t)j;
         if (taken == cap - 1 && fill + tot > cap) wcnt[NT / 64] = (uint32_t)(ASC ? j + 1 : j);
     }
     __syncthreads();
     if (fill + tot <= cap) {
         next = ASC ? pos + NT : (pos - NT > 0 ? pos - NT : 0);
     } else {
-        next = (int64_t)wcnt[NT / 64];
+        next = (int)wcnt[NT / 64];
         tot = cap - fill;
     }
     __syncthreads();                                          // wcnt is reused by the next round
-    return tot;
+    // uniform, and known to be: the batch loops stay scalar
+    next = __builtin_amdgcn_readfirstlane(next);
+    return __builtin_amdgcn_readfirstlane(tot);
 }
 
 // Front to back over the tile list; every thread owns one pixel.
-template <int TW, int NT, int MODE>
+template <int TW, int NT, int MODE, bool SCALAR>
 __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, int N, const float4* __restrict__ geom,
                                          const float4* __restrict__ app, const uint2* __restrict__ rect,
                                          const uint32_t* __restrict__ vals, const RasterConsts& rc,
-                                         FwdSmem<NT, MODE>& sm, PixFwd& st,
+                                         FwdSmem<NT, MODE, SCALAR>& sm, PixFwd& st,
                                          uint32_t* __restrict__ hits, float* __restrict__ max_alpha,
                                          float* __restrict__ max_weight, uint64_t& n_reached, uint64_t& n_blended,
                                          uint64_t& n_witer, uint64_t& n_wblend, uint64_t& n_upto_last,
@@ -356,14 +448,17 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
     st.T = 1.0f;
     st.C0 = st.C1 = st.C2 = st.N0 = st.N1 = st.N2 = st.S0 = st.S1 = st.S2 = st.zref = st.zmed = 0.f;
     st.last = st.kmed = 0;
-    uint32_t px_live = t.inside ? 1u : 0u;    // 0 once the pixel has terminated (or lies outside)
+    uint64_t px_live = ballot64(t.inside);    // the wave's pixels inside the image that have not terminated
     constexpr bool PLAIN = !COUNT && !HITS;
+    const int wv = wave_index();
+    const float4* geom_v = geom + kGeomF4 * (size_t)t.v * N;
+    const float4* app_v = SHADE || (CULL && !RECT) ? app + kAppF4 * (size_t)t.v * N : nullptr;
     // statistics of the previous batch's entries: every thread adds its own
     // slot to the global arrays (after a barrier), before the slot is reused
     int prev_cnt = 0;
     auto flush = [&]() {
         if (tid < prev_cnt && sm.st[0][tid] != 0u) {
-            const uint32_t g = sm.id[tid];
+            const uint32_t g = sm.id[tid] & kInstIdMask;
             atomicAdd(&hits[g], sm.st[0][tid]);
             if (STATS) {
                 atomicMax((uint32_t*)&max_alpha[g], sm.st[1][tid]);
@@ -372,70 +467,80 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
         }
     };
     // batches of up to NT entries of the tile, gathered from its group's run
-    int64_t pos = 0;
-    while (pos < (int64_t)t.n) {
-        if (__syncthreads_and(px_live == 0u)) break;
+    int pos = 0;
+    while (pos < t.n) {
+        // (gathering's barriers lie between this read and the next write)
+        if (lane == 0) sm.alive[wv] = px_live != 0ull ? 1u : 0u;
+        __syncthreads();
+        uint32_t alive = 0u;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) alive |= sm.alive[i];
+        if (__builtin_amdgcn_readfirstlane(alive) == 0u) break;
         if (HITS) flush();
         int cnt = 0;
-        while (cnt < NT && pos < (int64_t)t.n) {
-            int64_t next;
-            cnt += gather_round<NT, true>(t, vals, pos, cnt, NT, sm.a[0], sm.a[1], sm.wcnt, next);
+        while (cnt < NT && pos < t.n) {
+            int next;
+            cnt += gather_round<NT, true>(t, vals, pos, cnt, NT, sm.id, sm.pos, sm.wcnt, next);
             pos = next;
         }
         if (tid < cnt) {
-            const uint32_t gv = __float_as_uint(sm.a[0][tid].x);
-            const uint32_t jpos = __float_as_uint(sm.a[1][tid].z);
-            const uint32_t g = gv & kInstIdMask;
-            const size_t r = (size_t)t.v * N + g;
+            const uint32_t g = sm.id[tid] & kInstIdMask;
+            const uint32_t jpos = sm.pos[tid];
             float4 gq[kGeomF4];
 #pragma unroll
-            for (int q = 0; q < kGeomF4; ++q) {
-                gq[q] = geom[kGeomF4 * r + q];
-                sm.g[q][tid] = gq[q];
-            }
+            for (int q = 0; q < kGeomF4; ++q) gq[q] = geom_v[kGeomF4 * (size_t)g + q];
+            sm.rec.put(tid, gq, SHADE ? app_v + kAppF4 * (size_t)g : nullptr);
             uint32_t bits = (1u << (NT / 64)) - 1u;
-            float2 n12 = make_float2(0.f, 0.f);
-            if (RECT) {
-                // ushort4 rectangle (x_lo, x_hi, y_lo, y_hi) read as two packed ranges
-                const uint2 rr = rect[r];
-                const float4 a1 = make_float4(0.f, 0.f, __uint_as_float(rr.x), __uint_as_float(rr.y));
-                bits = wave_bits<TW, NT / 64>(gq[0], gq[1], gq[2], gq[3].w, a1, t.tx0, t.ty0);
-            } else if (CULL) {
-                const float4 a0 = app[kAppF4 * r], a1 = app[kAppF4 * r + 1];
-                // the appearance is stored first: fewer registers live across the bounds
-                sm.a[0][tid] = a0;
-                n12 = make_float2(a1.x, a1.y);
-                reinterpret_cast<float2*>(&sm.a[1][tid])[0] = n12;
-                bits = wave_bits<TW, NT / 64>(gq[0], gq[1], gq[2], gq[3].w, a1, t.tx0, t.ty0);
-                if (bitcache) bitcache_put<NT>(bitcache, jpos, bits);
+            if (CULL) {
+                // the pixel rectangle as two packed ranges: from the rectangle
+                // array, or the last two slots of the appearance record
+                const uint2 rr = RECT ? rect[(size_t)t.v * N + g]
+                                      : reinterpret_cast<const uint2*>(app_v + kAppF4 * (size_t)g)[3];
+                bits = wave_bits<TW, NT / 64>(gq[0], gq[1], gq[2], gq[3].w, rr, t.tx0, t.ty0);
+                if (!RECT && bitcache) bitcache_put<NT>(bitcache, jpos, bits);
             }
-            // the run position and the wave bits replace the packed rectangle
-            if (CULL && !RECT)
-                reinterpret_cast<float2*>(&sm.a[1][tid])[1] = make_float2(__uint_as_float(jpos), __uint_as_float(bits));
-            else
-                sm.a[1][tid] = make_float4(n12.x, n12.y, __uint_as_float(jpos), __uint_as_float(bits));
-            if (HITS) {
-                sm.id[tid] = g;
-                sm.st[0][tid] = 0u;
-            }
+            sm.id[tid] = g | (bits << SR_INST_ID_BITS);
+            sm.pos[tid] = jpos + 1u;
+            if (HITS) sm.st[0][tid] = 0u;
             if (STATS) {
                 sm.st[1][tid] = 0u;
                 sm.st[2][tid] = 0u;
             }
         }
         __syncthreads();
-        bool wave_done = ballot64(px_live != 0u) == 0ull;
+        bool wave_done = px_live == 0ull;
         for (int c = 0; c * 64 < cnt && !wave_done; ++c) {
-          uint64_t live = wave_live_mask(sm.a[1], c, cnt);
+          const int slot = c * 64 + lane;
+          const uint32_t my_id = slot < cnt ? sm.id[slot] : 0u, my_pos = sm.pos[slot];
+          uint64_t live = ballot64((my_id >> (SR_INST_ID_BITS + wv)) & 1u);
+          if (live == 0ull) continue;
+          // SCALAR: the records of the wave's entries, one ahead of the evaluation
+          int nbit = (int)__builtin_ctzll(live);
+          EntryRec next_rec;
+          if constexpr (SCALAR) {
+            load_scalar<SHADE, SHADE>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
+            next_rec.c = sm.rec.c[c * 64 + nbit];
+          }
           // HITS: this wave's blended pixels of entry c * 64 + lane
           uint32_t my_hits = 0;
           while (live != 0ull) {
-            const int bit = (int)__builtin_ctzll(live);
-            const int k = c * 64 + bit;
+            const int bit = nbit, k = c * 64 + bit;
+            EntryRec rec = next_rec;
             live &= live - 1ull;
+            nbit = live != 0ull ? (int)__builtin_ctzll(live) : bit;
+            uint32_t jidx;                         // run position + 1
+            if constexpr (SCALAR) {
+                load_scalar<SHADE, SHADE>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
+                jidx = __builtin_amdgcn_readlane(my_pos, bit);
+            } else {
+                load_lds<SHADE>(sm.rec, k, rec);
+                jidx = sm.pos[k];
+            }
+            const SurfelGeom sg = geom_of<SCALAR>(rec);
             PairEval e;
-            const float4 g2 = sm.g[2][k], g3 = sm.g[3][k];
-            eval_test(sm.g[0][k], sm.g[1][k], g2, g3, px, py, e);
+            eval_test<SCALAR>(sg, px, py, e);
+            // behind the last use of this entry's: the same registers
+            if constexpr (SCALAR) next_rec.c = sm.rec.c[c * 64 + nbit];
             // blends entry k into the pixel state (before the transmittance update)
             auto accumulate = [&](float wgt) {
                 // the depth reference of the distortion sums is the depth of
@@ -444,59 +549,58 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
                 st.zref = st.T == 1.0f ? e.z : st.zref;
                 const float zs = e.z - st.zref;
                 if (SHADE) {
-                    const float4 a0 = sm.a[0][k], a1 = sm.a[1][k];
-                    st.C0 = __builtin_fmaf(wgt, a0.x, st.C0);
-                    st.C1 = __builtin_fmaf(wgt, a0.y, st.C1);
-                    st.C2 = __builtin_fmaf(wgt, a0.z, st.C2);
-                    st.N0 = __builtin_fmaf(wgt, a0.w, st.N0);
-                    st.N1 = __builtin_fmaf(wgt, a1.x, st.N1);
-                    st.N2 = __builtin_fmaf(wgt, a1.y, st.N2);
+                    st.C0 = __builtin_fmaf(wgt, rec.a0.x, st.C0);
+                    st.C1 = __builtin_fmaf(wgt, rec.a0.y, st.C1);
+                    st.C2 = __builtin_fmaf(wgt, rec.a0.z, st.C2);
+                    st.N0 = __builtin_fmaf(wgt, rec.a0.w, st.N0);
+                    st.N1 = __builtin_fmaf(wgt, rec.a1.x, st.N1);
+                    st.N2 = __builtin_fmaf(wgt, rec.a1.y, st.N2);
                 }
                 st.S0 += wgt;
                 st.S1 = __builtin_fmaf(wgt, zs, st.S1);
                 st.S2 = __builtin_fmaf(wgt * zs, zs, st.S2);
-                const uint32_t jpos = __float_as_uint(sm.a[1][k].z);    // run position
                 if (MEDIAN && st.T > 0.5f) {         // T before this entry
                     st.zmed = e.z;
-                    st.kmed = jpos + 1u;
+                    st.kmed = jidx;
                 }
-                st.last = jpos + 1u;
+                st.last = jidx;
             };
             if (PLAIN) {
                 // no per-wave bookkeeping: the lanes that do not blend skip the
                 // block, and the wave skips it when none does
-                if (px_live != 0u && e.pass) {
-                    eval_finish(g2, g3, rc.alpha_max, e);
-                    const float Tn = st.T * (1.0f - e.a);
-                    if (Tn < rc.t_min) {
-                        px_live = 0u;
-                    } else {
-                        accumulate(e.a * st.T);
-                        st.T = Tn;
-                    }
+                float Tn = st.T;
+                if (in_mask(pass_mask(e) & px_live)) {
+                    eval_finish(sg, rc.alpha_max, e);
+                    Tn = st.T * (1.0f - e.a);
+                    if (!(Tn < rc.t_min)) accumulate(e.a * st.T);
                 }
-                if (ballot64(px_live != 0u) == 0ull) {
+                const uint64_t ended = ballot64(Tn < rc.t_min);
+                if (ended != 0ull) {
+                    Tn = in_mask(ended) ? st.T : Tn;
+                    px_live &= ~ended;
+                }
+                st.T = Tn;
+                if (px_live == 0ull) {
                     wave_done = true;
                     break;
                 }
                 continue;
             }
-            const bool done = px_live == 0u;
             if (COUNT) {
-                n_reached += (uint64_t)__popcll(ballot64(!done));
+                n_reached += (uint64_t)__popcll(px_live);
                 n_witer += 1;
-                n_eval += done ? 0u : 1u;
+                n_eval += in_mask(px_live) ? 1u : 0u;
             }
-            bool blend = !done && e.pass;
+            uint64_t bm = pass_mask(e) & px_live;
             // no pixel of this wave takes the entry: nothing changes
-            if (ballot64(blend) == 0ull) continue;
+            if (bm == 0ull) continue;
             if (COUNT) n_wblend += 1;
-            eval_finish(g2, g3, rc.alpha_max, e);
+            eval_finish(sg, rc.alpha_max, e);
             const float Tn = st.T * (1.0f - e.a);
-            if (blend && Tn < rc.t_min) {
-                px_live = 0u;
-                blend = false;
-            }
+            const uint64_t ended = bm & ballot64(Tn < rc.t_min);
+            px_live &= ~ended;
+            bm &= ~ended;
+            const bool blend = in_mask(bm);
             float wgt = 0.f;
             if (blend) {
                 wgt = e.a * st.T;
@@ -504,11 +608,10 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
                 st.T = Tn;
                 if (COUNT) n_eval_last = n_eval;
             }
-            if (COUNT) n_blended += (uint64_t)__popcll(ballot64(blend));
+            if (COUNT) n_blended += (uint64_t)__popcll(bm);
             if (HITS) {
-                const uint64_t bm = ballot64(blend);
                 if (bm != 0ull) {
-                    if (lane == bit) my_hits += (uint32_t)__popcll(bm);
+                    my_hits = (uint32_t)lane_write((int)__popcll(bm), bit, (int)my_hits);
                     if (STATS) {
                         // lane 0 holds the wave's max alpha, lane 32 its max weight
                         const uint32_t mx = wave_max2_bits(blend ? e.a : 0.f, wgt);
@@ -516,7 +619,7 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
                     }
                 }
             }
-            if (ballot64(px_live != 0u) == 0ull) {
+            if (px_live == 0ull) {
                 wave_done = true;
                 break;
             }
@@ -581,8 +684,8 @@ __device__ __forceinline__ void write_outputs(const PixFwd& st, const PixOut& o,
     n_contrib[o1] = st.last;
 }
 
-template <int TW, int TH, int MODE>
-__global__ void __launch_bounds__(TW * TH) SR_RASTER_OCCUPANCY
+template <int TW, int TH, int MODE, bool SCALAR>
+__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(!SCALAR ? kLdsWaves : (MODE & kShade) ? kFwdWaves : kPruneWaves)
 k_render_fwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __restrict__ geom,
              const float4* __restrict__ app, const uint2* __restrict__ rect, const uint32_t* __restrict__ vals,
              const uint2* __restrict__ ranges,
@@ -593,18 +696,18 @@ k_render_fwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __r
              float* __restrict__ median_depth, uint32_t* __restrict__ median_contrib,
              const uint32_t* __restrict__ tile_order, uint32_t* __restrict__ tile_cost) {
     constexpr int NT = TW * TH;
-    __shared__ FwdSmem<NT, MODE> sm;
+    __shared__ FwdSmem<NT, MODE, SCALAR> sm;
     __shared__ uint32_t s_cost;
     // an order entry beyond the grid leaves the workgroup idle
     if (tile_order && tile_order[blockIdx.x] >= gridDim.x) return;
     TileCtx t;
     tile_ctx<TW, TH>(cams, V, ranges, t, tile_order);
     const bool failed = status_failed(rc);
-    if (failed) t.n = 0u;
+    if (failed) t.n = 0;
     const float px = (float)t.ix + 0.5f, py = (float)t.iy + 0.5f;
     PixFwd st;
     uint64_t n_reached = 0, n_blended = 0, n_witer = 0, n_wblend = 0, n_upto = 0;
-    fwd_tile<TW, NT, MODE>(t, px, py, N, geom, app, rect, vals, rc, sm, st, hits, max_alpha, max_weight, n_reached,
+    fwd_tile<TW, NT, MODE, SCALAR>(t, px, py, N, geom, app, rect, vals, rc, sm, st, hits, max_alpha, max_weight, n_reached,
                            n_blended,
                        n_witer, n_wblend, n_upto);
     if (failed) poison(st);
@@ -659,32 +762,149 @@ __device__ __forceinline__ void pix_bwd_init(PixBwd& pb, const TileCtx& t, float
     pb.Wacc = (pb.gC0 * t.bg[0] + pb.gC1 * t.bg[1] + pb.gC2 * t.bg[2]) * Tf;
 }
 
+// A lane's part in wave_contract: quarter wave (lane & 3) holds one of four
+// values, b = lane >> 2 is its column of pixels 16 t + b (t = 0..3) of the
+// wave's 8x8 block, i.e. x = b % 8, y = 2 t + b / 8.
+struct ContractLane {
+    float x, y;         // of the column's middle, relative to the tile's
+    int slot;           // of the accumulator this lane adds to, or -1
+    int slot6;          // the same for wave_sum6, from slot 16 on
+};
+
+template <int TW, int TH>
+__device__ __forceinline__ ContractLane contract_lane() {
+    constexpr int WB = kWaveBlock;
+    const int lane = __lane_id(), b = lane >> 2, row = lane >> 4;
+    const int w = wave_index();
+    const int bx = (w % (TW / WB)) * WB, by = (w / (TW / WB)) * WB;
+    ContractLane c;
+    c.x = (float)(bx + (b & 7)) + 0.5f - 0.5f * TW;
+    c.y = (float)(by + (b >> 3)) + 3.5f - 0.5f * TH;      // mean of the four rows 2 t + b / 8
+    c.slot = (lane & 12) == 0 ? 4 * row + (lane & 3) : -1;
+    c.slot6 = (lane & 28) == 0 ? ((lane >> 5) == 0 ? (lane & 3) : ((lane & 2) == 0 ? 4 + (lane & 1) : -1)) : -1;
+    return c;
+}
+
+// Orders this wave's LDS accesses for the compiler (the LDS unit executes a
+// wave's accesses in order, so no wait is needed between its lanes).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The four values p of every lane, transposed in quarter waves: register t of
+// a lane is value lane & 3 of pixel 16 t + lane / 4.
+__device__ __forceinline__ float4 wave_transpose4(float* scr, const float4& p) {
+    const int lane = __lane_id();
+    wave_lds_order();
+    reinterpret_cast<float4*>(scr)[lane] = p;
+    wave_lds_order();
+    const float4 r = make_float4(scr[lane], scr[64 + lane], scr[128 + lane], scr[192 + lane]);
+    wave_lds_order();
+    return r;
+}
+
+// Sums over a wave of four values p, of each times y, of each times x (pixel
+// coordinates relative to the tile's middle), and of four values u, given
+// transposed as a and b: 16 sums, slots p 0..3, y p 4..7, x p 8..11, u 12..15
+// of acc.  Every lane sums four pixels of one value after the transposition
+// in LDS, so the products with x and y are formed once per four pixels and
+// the cross-lane stages (permlane swaps, row rotations) carry four registers:
+// 19 VALU instructions, where 11 products and a transposed reduction of 15
+// registers took 46.
+__device__ __forceinline__ float wave_contract(const ContractLane& c, const float4& a, const float4& b) {
+    const float S = (a.x + a.w) + (a.y + a.z);
+    // rows 2 t + b / 8: the offsets from their mean are -3, -1, 1, 3
+    const float Y = __builtin_fmaf(c.y, S, __builtin_fmaf(3.0f, a.w - a.x, a.z - a.y));
+    const float X = c.x * S;
+    const float U = (b.x + b.w) + (b.y + b.z);
+    const auto r0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(S), __float_as_uint(X), false, false);
+    const auto r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(Y), __float_as_uint(U), false, false);
+    const float s0 = __uint_as_float(r0[0]) + __uint_as_float(r0[1]);     // halves: S, X
+    const float s1 = __uint_as_float(r1[0]) + __uint_as_float(r1[1]);     // halves: Y, U
+    const auto r2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(s0), __float_as_uint(s1), false, false);
+    float w = __uint_as_float(r2[0]) + __uint_as_float(r2[1]);            // rows: S, Y, X, U
+    w += dpp_f<0x124, 0xF>(w);                  // row_ror:4
+    w += dpp_f<0x128, 0xF>(w);                  // row_ror:8
+    return w;
+}
+
+// The same for plain sums of six values: four transposed (a), two as the
+// sum q of two pixels of value lane & 1.
+__device__ __forceinline__ float wave_sum6(const float4& a, float q) {
+    const float P = (a.x + a.w) + (a.y + a.z);
+    q += dpp_f<0x4E, 0xF>(q);                   // quad_perm [2,3,0,1]
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(P), __float_as_uint(q), false, false);
+    const uint32_t h = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));    // halves: P, q
+    const auto r2 = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+    float w = __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
+    w += dpp_f<0x124, 0xF>(w);                  // row_ror:4
+    w += dpp_f<0x128, 0xF>(w);                  // row_ror:8
+    return w;
+}
+
+// The component of a gradient record that flush lane l adds, from the sums
+// of an entry (the slots of wave_contract and, 16 on, of wave_sum6):
+// scale * (acc[at] + offset * acc[shift >> 1]), the offset the x (even shift)
+// or y (odd) of the tile's middle from the projected centre.
+struct GradTerm {
+    int comp, at, shift;      // comp < 0: none; shift < 0: no offset term
+    float scale;
+};
+
+template <bool GEO>
+__device__ __forceinline__ GradTerm grad_term(int l) {
+    GradTerm t{-1, 0, -1, 1.0f};
+    if (l < 9) {
+        const int i = l % 3, kind = l / 3;               // dA: x sums, dB: y sums, dC'
+        t = GradTerm{l, kind == 0 ? 8 + i : (kind == 1 ? 4 + i : i), kind == 2 ? -1 : 2 * i + kind,
+                     i == 2 ? -1.0f : 1.0f};             // the walk sums -dL/dw2
+    } else if (l < 11) {
+        t = GradTerm{l, l == 9 ? 11 : 7, 2 * 3 + (l - 9), -2.0f};     // and -1/2 of the centre's
+    } else if (l == 11) {
+        t = GradTerm{11, 12, -1, 1.0f};
+    } else if (!GEO) {
+        if (l < 15) t = GradTerm{l + 3, l + 1, -1, 1.0f};             // colour
+    } else if (l < 21) {
+        t = GradTerm{l, l < 15 ? l + 4 : (l < 18 ? l - 2 : l + 1), -1, 1.0f};     // m_z, colour, normal
+    }
+    return t;
+}
+
 // Backward: per pixel, walk the tile list back to front from the last
 // blended entry, recovering T_k = T_{k+1} / (1 - a_k).  With g_k the
-// derivative of the loss by the blending weight w_k of entry k and
+// derivative of the loss by the blending weight w_k = a_k T_k of entry k and
 // W_k = sum_{j>k} g_j w_j (+ the background term), dL/da_k = T_k g_k -
-// W_k / (1 - a_k).  Per-record gradients are summed over each wave by
-// transposition (permlane swaps and DPP), over the workgroup in LDS, then
-// added to grad_rec with one atomic per (tile, record, component); with
-// grad_marks (the projection's tiles_touched) bit 31 of every record given a
-// gradient is set.
+// W_k / (1 - a_k).  Per-record gradients are summed over each wave
+// (wave_contract), over the workgroup in LDS, then added to grad_rec with one
+// atomic per (tile, record, component); with grad_marks (the projection's
+// tiles_touched) bit 31 of every record given a gradient is set.
 // GEO: the loss has depth, normal or distortion terms (their upstream
 // gradients are read); without them the depth path and six of the per-record
 // components are identically zero and are not computed or reduced.
 // HITS (without GEO): the backward also counts, per entry, the pixels that
 // blend it (the forward's blend decisions, recomputed: positions below the
-// pixel's last contributor that pass the cutoff), in the free component of
-// the wave reduction, and adds the count to hits[g] at the flush.
-template <int TW, int NT, int BATCH, bool GEO, bool HITS = false>
+// pixel's last contributor that pass the cutoff): the wave's count of an
+// entry is kept by the lane of the entry's position in its 64-entry chunk,
+// added to the workgroup's once per chunk and to hits[g] at the flush.
+//
+// VALU issue bounds this walk (one wave64 instruction per CU and cycle), and
+// the sums over the wave's 64 pixels were half of it.  They are a
+// contraction of a few per-pixel values with functions of the pixel that do
+// not depend on the entry: the columns A, B, C' of dL/dw and the low-pass
+// centre are the sums of {dw0, dw1, dw2, f2} times {x, y, 1}, so only those
+// four values and four plain sums (opacity, colour) go through the
+// reduction, not 15 products.
+template <int TW, int NT, int BATCH, bool GEO, bool SCALAR, bool HITS>
 __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, int N, const float4* __restrict__ geom,
                                          const float4* __restrict__ app, const uint32_t* __restrict__ vals,
-                                         const RasterConsts& rc, BwdSmem<BATCH>& sm, PixBwd pb,
+                                         const RasterConsts& rc, BwdSmem<NT, BATCH, GEO, HITS, SCALAR>& sm, PixBwd pb,
                                          float* __restrict__ grad_rec, uint32_t* __restrict__ grad_marks,
                                          uint32_t* __restrict__ hits = nullptr,
                                          uint32_t* __restrict__ cost_out = nullptr,
                                          const uint32_t* bitcache = nullptr) {
     static_assert(BATCH <= NT, "one record per thread and batch");
-    static_assert(!(HITS && GEO), "the count takes a component slot of the depth terms");
+    static_assert(!(HITS && GEO), "the count is taken by the training step alone");
     const int tid = threadIdx.x;
     const int lane = __lane_id();
     __syncthreads();
@@ -692,7 +912,7 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
     __syncthreads();
     atomicMax(&sm.maxn, pb.ncon);
     __syncthreads();
-    const uint32_t maxn = sm.maxn;
+    const uint32_t maxn = __builtin_amdgcn_readfirstlane(sm.maxn);
     // the tile's cost for the next launch's order: the run positions it works through
     if (cost_out && tid == 0) *cost_out = maxn;
     if (maxn == 0u) return;
@@ -704,153 +924,196 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
         wave_maxn = o > wave_maxn ? o : wave_maxn;
     }
     wave_maxn = __builtin_amdgcn_readfirstlane(wave_maxn);   // uniform: keep the loop control scalar
+    constexpr int TH = NT / TW;
     float T = pb.T, Wacc = pb.Wacc;
+    const int wv = wave_index();
+    const float4* geom_v = geom + kGeomF4 * (size_t)t.v * N;
+    const float4* app_v = app + kAppF4 * (size_t)t.v * N;
+    float* scr = reinterpret_cast<float*>(&sm.xp[64 * wv]);
+    const ContractLane cr = contract_lane<TW, TH>();
     static_assert(NT / 64 <= kMaxWaves, "gathering counts");
     // batches of up to BATCH entries of the tile below run position hi,
     // gathered from its group's run highest first into slots [lo, BATCH)
-    int64_t hi = maxn;
+    int hi = (int)maxn;
     while (hi > 0) {
         __syncthreads();
         int fill = 0;
         while (fill < BATCH && hi > 0) {
-            int64_t next;
-            fill += gather_round<NT, false>(t, vals, hi, fill, BATCH, sm.a[0], sm.a[1], sm.wcnt, next);
+            int next;
+            fill += gather_round<NT, false>(t, vals, hi, fill, BATCH, sm.id, sm.pos, sm.wcnt, next);
             hi = next;
         }
         const int lo = BATCH - fill;
         if (tid < BATCH) {
             if (tid >= lo) {
-                const uint32_t gv = __float_as_uint(sm.a[0][tid].x);
-                const uint32_t jpos = __float_as_uint(sm.a[1][tid].z);
-                const size_t r = (size_t)t.v * N + (gv & kInstIdMask);
+                const uint32_t g = sm.id[tid] & kInstIdMask;
+                const uint32_t jpos = sm.pos[tid];
                 float4 gq[kGeomF4];
 #pragma unroll
-                for (int q = 0; q < kGeomF4; ++q) {
-                    gq[q] = geom[kGeomF4 * r + q];
-                    sm.g[q][tid] = gq[q];
-                }
-                const float4 a0 = app[kAppF4 * r], a1 = app[kAppF4 * r + 1];
-                sm.a[0][tid] = a0;
-                reinterpret_cast<float2*>(&sm.a[1][tid])[0] = make_float2(a1.x, a1.y);
+                for (int q = 0; q < kGeomF4; ++q) gq[q] = geom_v[kGeomF4 * (size_t)g + q];
+                sm.rec.put(tid, gq, app_v + kAppF4 * (size_t)g);
+                sm.mid[tid] = make_float2((float)(t.tx0 + TW / 2) - gq[2].y, (float)(t.ty0 + TH / 2) - gq[2].z);
                 // the forward's wave bits of this position when cached
                 const uint32_t bits = (bitcache && jpos < BitCache<NT>::kPos)
                                           ? (bitcache[jpos >> 3] >> ((jpos & 7u) << 2)) & 0xFu
-                                          : wave_bits<TW, NT / 64>(gq[0], gq[1], gq[2], gq[3].w, a1, t.tx0, t.ty0);
-                // entries at or beyond the wave's last contributor concern no lane of it
-                reinterpret_cast<float2*>(&sm.a[1][tid])[1] = make_float2(__uint_as_float(jpos), __uint_as_float(bits));
-                sm.rec[tid] = (uint32_t)r;
+                                          : wave_bits<TW, NT / 64>(gq[0], gq[1], gq[2], gq[3].w,
+                                                                   reinterpret_cast<const uint2*>(app_v + kAppF4 * (size_t)g)[3],
+                                                                   t.tx0, t.ty0);
+                sm.id[tid] = g | (bits << SR_INST_ID_BITS);
             }
 #pragma unroll
-            for (int i = 0; i < kNumGrad; ++i) sm.acc[tid][i] = 0.f;
+            for (int i = 0; i < (GEO ? 22 : 16); ++i) sm.acc[tid][i] = 0.f;
+            if (HITS) sm.hit[tid] = 0u;
+            if (tid < (BATCH + 63) / 64) sm.touched[tid] = 0ull;
         }
         __syncthreads();
         // entries skipped by the forward for this wave are skipped here too
         for (int c = (BATCH - 1) >> 6; c >= (lo >> 6); --c) {
-          uint64_t live = wave_live_mask_from(sm.a[1], c, lo, BATCH, wave_maxn);
+          // entries at or beyond the wave's last contributor concern no lane of it
+          const int slot = c * 64 + lane;
+          const bool in = slot >= lo && slot < BATCH;
+          const uint32_t my_id = in ? sm.id[slot] : 0u, my_pos = in ? sm.pos[slot] : 0u;
+          uint64_t live = ballot64(((my_id >> (SR_INST_ID_BITS + wv)) & 1u) && my_pos < wave_maxn);
+          if (live == 0ull) continue;
+          int nbit = 63 - (int)__builtin_clzll(live);
+          EntryRec next_rec;
+          if constexpr (SCALAR) {
+            load_scalar<true, GEO>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
+            next_rec.c = sm.rec.c[c * 64 + nbit];
+          }
+          uint32_t my_hits = 0;       // HITS: this wave's blended pixels of entry c * 64 + lane
+          uint64_t blended = 0ull;    // the chunk's entries that a pixel of the wave blends
           while (live != 0ull) {
-            const int hb = 63 - (int)__builtin_clzll(live);
+            const int hb = nbit, k = c * 64 + hb;
+            EntryRec rec = next_rec;
             live &= ~(1ull << hb);
-            const int k = c * 64 + hb;
-            const uint32_t jj = __float_as_uint(sm.a[1][k].z);    // run position
+            nbit = live != 0ull ? 63 - (int)__builtin_clzll(live) : hb;
+            uint32_t jj;                           // run position
+            if constexpr (SCALAR) {
+                load_scalar<true, GEO>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
+                jj = __builtin_amdgcn_readlane(my_pos, hb);
+            } else {
+                load_lds<true>(sm.rec, k, rec);
+                jj = sm.pos[k];
+            }
+            const SurfelGeom sg = geom_of<SCALAR>(rec);
             PairEval e;
-            const float4 g2 = sm.g[2][k], g3 = sm.g[3][k];
-            eval_test(sm.g[0][k], sm.g[1][k], g2, g3, px, py, e);
-            const bool bl = (jj < pb.ncon) && e.pass;
-            if (ballot64(bl) == 0ull) continue;
-            eval_finish(g2, g3, rc.alpha_max, e);
+            eval_test<SCALAR>(sg, px, py, e);
+            // behind the last use of this entry's: the same registers
+            if constexpr (SCALAR) next_rec.c = sm.rec.c[c * 64 + nbit];
+            const uint64_t blm = ballot64(jj < pb.ncon) & pass_mask(e);
+            if (blm == 0ull) continue;
+            blended |= 1ull << hb;
+            const bool bl = in_mask(blm);
+            eval_finish(sg, rc.alpha_max, e);
             // Gradients of this entry, branch-free: lanes that do not blend it
-            // produce exact zeros (dL/da and the weight are selected to 0, the
-            // intersection terms of low-pass lanes are selected away).
-            const float4 a0 = sm.a[0][k], a1 = sm.a[1][k];
-            const float o = g2.w;
-            const float rin = __builtin_amdgcn_rcpf(1.0f - e.a);
-            const float Tk = T * rin;
-            const float wraw = e.a * Tk;
-            const float wgt = bl ? wraw : 0.f;
+            // produce exact zeros (alpha, dL/do and the intersection terms are
+            // selected to 0, and W only steps where they blend).
+            const F4v a0 = rec.a0;
+            const float o = sg.o;
+            const float ae = bl ? e.a : 0.f;
+            const float rin = __builtin_amdgcn_rcpf(1.0f - ae);
+            T = T * rin;                                  // T before this entry; unchanged where ae = 0
+            const float wgt = ae * T;
             float gk = pb.gC0 * a0.x + pb.gC1 * a0.y + pb.gC2 * a0.z + pb.gA;
             float dLdz = 0.f;
-            float gr[kNumGrad];
             if (GEO) {
                 const float zr = e.z - pb.rmean;
-                gk += pb.gD * e.z + pb.gN0 * a0.w + pb.gN1 * a1.x + pb.gN2 * a1.y +
+                gk += pb.gD * e.z + pb.gN0 * a0.w + pb.gN1 * rec.a1.x + pb.gN2 * rec.a1.y +
                       pb.gS * 2.0f * (pb.Q + pb.S0 * zr * zr);
                 // the median depth is the depth of entry kmed - 1 (0-based)
                 const float gmed = jj + 1u == pb.kmed ? pb.gMed : 0.f;
-                dLdz = bl ? __builtin_fmaf(wraw, pb.gD + 4.0f * pb.gS * pb.S0 * zr, gmed) : 0.f;
-                gr[18] = pb.gN0 * wgt; gr[19] = pb.gN1 * wgt; gr[20] = pb.gN2 * wgt;
+                dLdz = bl ? __builtin_fmaf(wgt, pb.gD + 4.0f * pb.gS * pb.S0 * zr, gmed) : 0.f;
             }
-            const float dLda = bl ? Tk * gk - Wacc * rin : 0.f;
-            Wacc = bl ? __builtin_fmaf(gk, wraw, Wacc) : Wacc;
-            T = bl ? Tk : T;
-            gr[15] = pb.gC0 * wgt; gr[16] = pb.gC1 * wgt; gr[17] = pb.gC2 * wgt;
-            const float dLdo = e.clamped ? 0.f : dLda * e.G;
-            const float dLdG = e.clamped ? 0.f : dLda * o;
-            gr[11] = dLdo;
-            const float dLdrho = -e.G * dLdG;
+            const float dLda = T * gk - Wacc * rin;
+            Wacc = bl ? __builtin_fmaf(gk, wgt, Wacc) : Wacc;
+            const float dLdo = bl && !e.clamped ? dLda * e.G : 0.f;
+            const float dLdrho = -(o * dLdo);
             const float us = e.surf ? e.u : 0.f, vs = e.surf ? e.v : 0.f, rs = e.surf ? e.r : 0.f;
-            float du = dLdrho * us, dv = dLdrho * vs;
+            float dw0, dw1, dw2, dzs = 0.f;
             if (GEO) {
-                const float dzs = e.surf ? dLdz : 0.f;
-                du += dzs * g3.x;
-                dv += dzs * g3.y;
-                gr[12] = dzs * us; gr[13] = dzs * vs; gr[14] = dLdz;
+                dzs = e.surf ? dLdz : 0.f;
+                const float du = __builtin_fmaf(dzs, sg.m30, dLdrho * us), dv = __builtin_fmaf(dzs, sg.m31, dLdrho * vs);
+                dw0 = du * rs;
+                dw1 = dv * rs;
+            } else {
+                const float m = dLdrho * rs;
+                dw0 = m * us;
+                dw1 = m * vs;
             }
-            const float dw0 = du * rs, dw1 = dv * rs;
-            const float dw2 = -(du * us + dv * vs) * rs;
-            gr[0] = dw0 * e.dx; gr[1] = dw1 * e.dx; gr[2] = dw2 * e.dx;
-            gr[3] = dw0 * e.dy; gr[4] = dw1 * e.dy; gr[5] = dw2 * e.dy;
-            gr[6] = dw0; gr[7] = dw1; gr[8] = dw2;
-            const float f2 = e.surf ? 0.f : -2.0f * dLdrho;
-            gr[9] = f2 * e.dx;
-            gr[10] = f2 * e.dy;
-            // Wave totals by transposition; the lanes holding distinct
-            // components add them into the workgroup accumulator.
-            {
-                float c16[16];
-#pragma unroll
-                for (int i = 0; i < 12; ++i) c16[i] = gr[i];
-                c16[12] = gr[15]; c16[13] = gr[16]; c16[14] = gr[17];
-                // HITS: the blending pixels, summed exactly (at most 64 per wave)
-                c16[15] = HITS && bl ? 1.f : 0.f;
-                const float tot = wave_tsum<16>(c16);
-                const int ci = wave_tsum_comp<16>(lane);
-                // components 12..14 go to slots 15..17; the count to slot 12 (a depth slot)
-                if ((lane & 12) == 0 && ci < (HITS ? 16 : 15))
-                    atomicAdd(&sm.acc[k][ci < 12 ? ci : (ci < 15 ? ci + 3 : 12)], tot);
-            }
+            dw2 = __builtin_fmaf(dw0, us, dw1 * vs);          // -dL/dw2
+            const float f2 = e.surf ? 0.f : dLdrho;           // -1/2 of the centre's
+            const float4 ta = wave_transpose4(scr, make_float4(dw0, dw1, dw2, f2));
+            const float4 tb = wave_transpose4(scr, make_float4(dLdo, pb.gC0 * wgt, pb.gC1 * wgt, pb.gC2 * wgt));
+            float w6 = 0.f;
             if (GEO) {
-                float c8[8] = {gr[12], gr[13], gr[14], gr[18], gr[19], gr[20], 0.f, 0.f};
-                const float tot = wave_tsum<8>(c8);
-                const int ci = wave_tsum_comp<8>(lane);
-                if ((lane & 14) == 0 && ci < 6) atomicAdd(&sm.acc[k][ci < 3 ? 12 + ci : 15 + ci], tot);
+                const float4 tc = wave_transpose4(scr, make_float4(dzs * us, dzs * vs, dLdz, pb.gN0 * wgt));
+                reinterpret_cast<float2*>(scr)[lane] = make_float2(pb.gN1 * wgt, pb.gN2 * wgt);
+                wave_lds_order();
+                const float q = scr[lane] + scr[64 + lane];      // value lane & 1 of two pixels
+                wave_lds_order();
+                w6 = wave_sum6(tc, q);
             }
+            float w16 = wave_contract(cr, ta, tb);
+            // summed before the branches: sunk below them, the last adds need moves of their own
+            asm volatile("" : "+v"(w16), "+v"(w6));
+            if (cr.slot >= 0) atomicAdd(&sm.acc[k][cr.slot], w16);
+            if (GEO && cr.slot6 >= 0) atomicAdd(&sm.acc[k][16 + cr.slot6], w6);
+            if (HITS) my_hits = (uint32_t)lane_write((int)__popcll(blm), hb, (int)my_hits);
           }
+          if (HITS && my_hits != 0u) atomicAdd(&sm.hit[c * 64 + lane], my_hits);
+          if (lane == 0 && blended != 0ull) atomicOr((unsigned long long*)&sm.touched[c], (unsigned long long)blended);
         }
         __syncthreads();
-        if (tid >= lo && tid < BATCH) {
-            float* dst = grad_rec + (size_t)sm.rec[tid] * SR_GRAD_STRIDE;
-            bool any = false;
+        // The batch's sums to memory.  The lanes of a quarter (half with GEO)
+        // wave hold the components of one record, so its atomics leave as two
+        // requests of adjacent words: with a lane per record every component
+        // was a request of its own, and their rate bounded the backward (k_render_bwd
+        // with the depth terms, four 1559x1039 views of 1M surfels: 2.3 ms
+        // without any atomics, 3.5 ms with 21 requests a record).
+        constexpr int LPR = GEO ? 32 : 16;              // lanes per record
+        // the entries that were blended at all, listed by every wave for itself
+        int* list = reinterpret_cast<int*>(scr);
+        int touched = 0;
+        wave_lds_order();
 #pragma unroll
-            for (int i = 0; i < kNumGrad; ++i) {
-                if (HITS && i == 12) continue;
-                const float vsum = sm.acc[tid][i];
-                if (vsum != 0.f) {
-                    atomicAdd(&dst[i], vsum);
-                    any = true;
-                }
+        for (int c = 0; c < (BATCH + 63) / 64; ++c) {
+            const uint64_t m = sm.touched[c];
+            if (in_mask(m)) list[touched + __popcll(m & (lane == 0 ? 0ull : ~0ull >> (64 - lane)))] = c * 64 + lane;
+            touched += (int)__popcll(m);
+        }
+        wave_lds_order();
+        int fl = tid & (LPR - 1);
+        asm volatile("" : "+v"(fl));      // the term is formed here, not kept in registers through the walk
+        const GradTerm term = grad_term<GEO>(fl);
+        for (int n = tid / LPR; n < touched; n += NT / LPR) {
+            const int e = list[n];
+            const uint32_t g = sm.id[e] & kInstIdMask;
+            const size_t r = (size_t)t.v * N + g;
+            // the sums refer to the tile's middle: dx = (px - middle) + (middle - cx)
+            const float* A = sm.acc[e];
+            float v = 0.f;
+            if (term.comp >= 0) {
+                v = A[term.at];
+                if (term.shift >= 0) v = __builtin_fmaf(term.shift & 1 ? sm.mid[e].y : sm.mid[e].x, A[term.shift >> 1], v);
+                v *= term.scale;
+                if (v != 0.f) atomicAdd(&grad_rec[r * SR_GRAD_STRIDE + term.comp], v);
             }
             // mark the record for the projection backward (bit 31)
-            if (grad_marks && any) atomicOr(&grad_marks[sm.rec[tid]], 0x80000000u);
-            if (HITS) {
-                const uint32_t n = (uint32_t)sm.acc[tid][12];
-                if (n != 0u) atomicAdd(&hits[sm.rec[tid] - (uint32_t)t.v * (uint32_t)N], n);
+            const uint64_t any = ballot64(v != 0.f) & ((LPR == 32 ? 0xFFFFFFFFull : 0xFFFFull) << (lane & ~(LPR - 1)));
+            if (fl == 0) {
+                if (grad_marks && any != 0ull) atomicOr(&grad_marks[r], 0x80000000u);
+                if (HITS) {
+                    const uint32_t n = sm.hit[e];
+                    if (n != 0u) atomicAdd(&hits[g], n);
+                }
             }
         }
     }
 }
 
-template <int TW, int TH, int BATCH, bool GEO>
-__global__ void __launch_bounds__(TW * TH) SR_RASTER_OCCUPANCY
+template <int TW, int TH, int BATCH, bool GEO, bool SCALAR>
+__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(kBwdWaves)
 k_render_bwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __restrict__ geom,
              const float4* __restrict__ app, const uint32_t* __restrict__ vals, const uint2* __restrict__ ranges,
              RasterConsts rc, const float* __restrict__ alpha, const float* __restrict__ depth,
@@ -860,7 +1123,7 @@ k_render_bwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __r
              const uint32_t* __restrict__ median_contrib, const float* __restrict__ dMed,
              float* __restrict__ grad_rec, uint32_t* __restrict__ grad_marks,
              const uint32_t* __restrict__ tile_order) {
-    __shared__ BwdSmem<BATCH> sm;
+    __shared__ BwdSmem<TW * TH, BATCH, GEO, false, SCALAR> sm;
     // an order entry beyond the grid leaves the workgroup idle; so does a set
     // status word (no gradients)
     if (tile_order && tile_order[blockIdx.x] >= gridDim.x) return;
@@ -885,7 +1148,7 @@ k_render_bwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __r
         if (dMed) { pb.gMed = dMed[o1]; pb.kmed = median_contrib[o1]; }
         pix_bwd_init(pb, t, T_final[o1], n_contrib[o1], alpha[o1], depth[o1], dist[o1]);
     }
-    bwd_tile<TW, TW * TH, BATCH, GEO>(t, px, py, N, geom, app, vals, rc, sm, pb, grad_rec, grad_marks);
+    bwd_tile<TW, TW * TH, BATCH, GEO, SCALAR, false>(t, px, py, N, geom, app, vals, rc, sm, pb, grad_rec, grad_marks);
 }
 
 // One training step of the compositing for a tile: forward, the masked L1 +
@@ -896,8 +1159,8 @@ k_render_bwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __r
 // STATS = 2 has the forward take the count and the maximum alpha and weight;
 // 0 records nothing.  Per-tile loss partial sums go to tile_loss[2*tile]
 // (L_b numerator, L1 numerator).
-template <int TW, int TH, int BATCH, int STATS>
-__global__ void __launch_bounds__(TW * TH) SR_RASTER_OCCUPANCY
+template <int TW, int TH, int BATCH, int STATS, bool SCALAR>
+__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(SCALAR ? kTrainWaves : kLdsWaves)
 k_train_raster(const sr_camera* __restrict__ cams, int V, int N, const float4* __restrict__ geom,
                const float4* __restrict__ app, const uint32_t* __restrict__ vals, const uint2* __restrict__ ranges,
                RasterConsts rc, const uint8_t* __restrict__ mask, const float* __restrict__ target, float gamma,
@@ -909,9 +1172,11 @@ k_train_raster(const sr_camera* __restrict__ cams, int V, int N, const float4* _
                const uint32_t* __restrict__ tile_order, uint32_t* __restrict__ tile_cost) {
     constexpr int NT = TW * TH;
     constexpr int MODE = kShade | (STATS == 2 ? kStats : 0);
-    constexpr size_t kF = sizeof(FwdSmem<NT, MODE>), kB = sizeof(BwdSmem<BATCH>);
+    using FSmem = FwdSmem<NT, MODE, SCALAR>;
+    using BSmem = BwdSmem<NT, BATCH, false, STATS == 1, SCALAR>;
+    constexpr size_t kF = sizeof(FSmem), kB = sizeof(BSmem);
     __shared__ __align__(16) unsigned char smem[kF > kB ? kF : kB];
-    __shared__ float s_red[NT];
+    __shared__ float s_red[NT / 64][2];
     // the wave-bit cache, except with the full statistics (whose larger
     // forward staging would lose a workgroup per CU to the extra LDS)
     constexpr bool CACHE = STATS != 2;
@@ -923,7 +1188,7 @@ k_train_raster(const sr_camera* __restrict__ cams, int V, int N, const float4* _
     tile_ctx<TW, TH>(cams, V, ranges, t, tile_order);
     // a set status word: nothing blended, NaN outputs and losses, no gradients
     const bool failed = status_failed(rc);
-    if (failed) t.n = 0u;
+    if (failed) t.n = 0;
     const float px = (float)t.ix + 0.5f, py = (float)t.iy + 0.5f;
     PixFwd st;
     uint64_t n0 = 0, n1 = 0, n2 = 0, n3 = 0, n4 = 0;
@@ -931,7 +1196,7 @@ k_train_raster(const sr_camera* __restrict__ cams, int V, int N, const float4* _
         for (int i = threadIdx.x; i < BitCache<NT>::kWords; i += NT) s_bits[i] = 0u;
         __syncthreads();
     }
-    fwd_tile<TW, NT, MODE>(t, px, py, N, geom, app, nullptr, vals, rc, *reinterpret_cast<FwdSmem<NT, MODE>*>(smem), st,
+    fwd_tile<TW, NT, MODE, SCALAR>(t, px, py, N, geom, app, nullptr, vals, rc, *reinterpret_cast<FSmem*>(smem), st,
                            hits, max_alpha, max_weight, n0, n1, n2, n3, n4, CACHE ? s_bits : nullptr);
     if (failed) poison(st);
     const PixOut o = pix_outputs(st, t);
@@ -954,25 +1219,25 @@ k_train_raster(const sr_camera* __restrict__ cams, int V, int N, const float4* _
         pb.gC0 = gC[0]; pb.gC1 = gC[1]; pb.gC2 = gC[2];
         pix_bwd_init(pb, t, st.T, st.last, o.A, o.D, o.Dist);
     }
-    // per-tile loss partials, fixed-order tree
-    __syncthreads();
-    s_red[threadIdx.x] = lb;
-    __syncthreads();
-    for (int off = NT / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) s_red[threadIdx.x] += s_red[threadIdx.x + off];
-        __syncthreads();
+    // per-tile loss partials, in a fixed order: over the wave, then the waves
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        lb += __shfl_xor(lb, off, 64);
+        l1 += __shfl_xor(l1, off, 64);
     }
-    if (threadIdx.x == 0) tile_loss[2 * (size_t)t.tile] = s_red[0];
-    __syncthreads();
-    s_red[threadIdx.x] = l1;
-    __syncthreads();
-    for (int off = NT / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) s_red[threadIdx.x] += s_red[threadIdx.x + off];
-        __syncthreads();
+    if (__lane_id() == 0) {
+        s_red[threadIdx.x >> 6][0] = lb;
+        s_red[threadIdx.x >> 6][1] = l1;
     }
-    if (threadIdx.x == 0) tile_loss[2 * (size_t)t.tile + 1] = s_red[0];
-    bwd_tile<TW, NT, BATCH, false, STATS == 1>(t, px, py, N, geom, app, vals, rc,
-                                               *reinterpret_cast<BwdSmem<BATCH>*>(smem), pb, grad_rec, grad_marks, hits,
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) sum += s_red[i][threadIdx.x];
+        tile_loss[2 * (size_t)t.tile + threadIdx.x] = sum;
+    }
+    bwd_tile<TW, NT, BATCH, false, SCALAR, STATS == 1>(t, px, py, N, geom, app, vals, rc,
+                                               *reinterpret_cast<BSmem*>(smem), pb, grad_rec, grad_marks, hits,
                                                tile_cost ? tile_cost + t.tile : nullptr, CACHE ? s_bits : nullptr);
 }
 
@@ -1014,6 +1279,18 @@ bool with_batch(int batch, F&& f) {
     return false;
 }
 
+// Where the entries' records are read from (EntryRec): through the scalar
+// cache from this many pixels of tiles on, from LDS below.  With fewer tiles a
+// SIMD holds one or two waves and the scalar loads' latency shows; with more,
+// the other waves cover it and the LDS reads would fill the LDS unit.
+// Measured (scalar / LDS): training step of 16.6 Mpx 8.27 / 9.39 ms, of one
+// 800x800 view 0.703 / 0.706, of three small views 3.72 / 3.35; backward with
+// the depth terms in iterations of 800x600 1.136 / 1.148 and of two 441x280
+// views 3.87 / 3.68; forwards of 6.5 Mpx (in a 4-view Eq. 3 pass) 4.99 / 5.40,
+// of one 1237x822 view 0.692 / 0.684, of one 131x145 view 4.29 / 3.86.
+constexpr int64_t kScalarFwdPixels = 2000000, kScalarBwdPixels = 450000;
+inline bool scalar_records(int64_t pixels, int64_t from) { return pixels >= from; }
+
 template <int TW, int TH, int MODE>
 void fwd_launch(int total_tiles, hipStream_t s, const sr_camera* cams, int V, int N, const float4* geom,
                 const float4* app, const uint2* rect, const uint32_t* vals, const uint2* ranges, RasterConsts rc,
@@ -1021,7 +1298,9 @@ void fwd_launch(int total_tiles, hipStream_t s, const sr_camera* cams, int V, in
                 float* alpha, float* depth, float* normal, float* dist, float* T_final, uint32_t* n_contrib,
                 uint32_t* hits, float* max_alpha, float* max_weight, unsigned long long* counts,
                 float* median_depth, uint32_t* median_contrib, const uint32_t* tile_order, uint32_t* tile_cost) {
-    hipLaunchKernelGGL((k_render_fwd<TW, TH, MODE>), dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app,
+    auto k = scalar_records((int64_t)total_tiles * TW * TH, kScalarFwdPixels) ? k_render_fwd<TW, TH, MODE, true>
+                                                                      : k_render_fwd<TW, TH, MODE, false>;
+    hipLaunchKernelGGL(k, dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app,
                        rect, vals, ranges, rc, color, alpha, depth, normal, dist, T_final, n_contrib, hits, max_alpha,
                        max_weight, counts, median_depth, median_contrib, tile_order, tile_cost);
 }
@@ -1062,14 +1341,12 @@ bool bwd_launch(int batch, int total_tiles, hipStream_t s, const sr_camera* cams
     const bool geo = dD || dN || dS || dMed;
     return with_batch<TW * TH>(resolve_batch(TW * TH, batch), [&](auto bc) {
         constexpr int B = decltype(bc)::value;
-        if (geo)
-            hipLaunchKernelGGL((k_render_bwd<TW, TH, B, true>), dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N,
-                               geom, app, vals, ranges, rc, alpha, depth, dist, T_final, n_contrib, dC, dA, dD, dN,
-                               dS, median_contrib, dMed, grad_rec, grad_marks, tile_order);
-        else
-            hipLaunchKernelGGL((k_render_bwd<TW, TH, B, false>), dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N,
-                               geom, app, vals, ranges, rc, alpha, depth, dist, T_final, n_contrib, dC, dA, dD, dN,
-                               dS, median_contrib, dMed, grad_rec, grad_marks, tile_order);
+        const bool sc = scalar_records((int64_t)total_tiles * TW * TH, kScalarBwdPixels);
+        auto k = geo ? (sc ? k_render_bwd<TW, TH, B, true, true> : k_render_bwd<TW, TH, B, true, false>)
+                     : (sc ? k_render_bwd<TW, TH, B, false, true> : k_render_bwd<TW, TH, B, false, false>);
+        hipLaunchKernelGGL(k, dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app, vals, ranges, rc, alpha,
+                           depth, dist, T_final, n_contrib, dC, dA, dD, dN, dS, median_contrib, dMed, grad_rec,
+                           grad_marks, tile_order);
     });
 }
 
@@ -1083,10 +1360,12 @@ bool train_launch(int stats, int batch, int total_tiles, hipStream_t s, const sr
                   uint32_t* tile_cost) {
     return with_batch<TW * TH>(resolve_batch(TW * TH, batch), [&](auto bc) {
         constexpr int B = decltype(bc)::value;
+        const bool sc = scalar_records((int64_t)total_tiles * TW * TH, kScalarBwdPixels);
 #define SR_TRAIN(S)                                                                                              \
-    hipLaunchKernelGGL((k_train_raster<TW, TH, B, S>), dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, \
-                       app, vals, ranges, rc, mask, target, gamma, w_c, color, alpha, depth, normal, dist, T_final, \
-                       n_contrib, hits, max_alpha, max_weight, tile_loss, grad_rec, grad_marks, tile_order, tile_cost)
+    hipLaunchKernelGGL((sc ? k_train_raster<TW, TH, B, S, true> : k_train_raster<TW, TH, B, S, false>),         \
+                       dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app, vals, ranges, rc, mask,    \
+                       target, gamma, w_c, color, alpha, depth, normal, dist, T_final, n_contrib, hits, max_alpha, \
+                       max_weight, tile_loss, grad_rec, grad_marks, tile_order, tile_cost)
         if (stats == 2)
             SR_TRAIN(2);
         else if (stats == 1)

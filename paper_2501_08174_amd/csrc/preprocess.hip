@@ -343,7 +343,7 @@ k_preprocess(int N, const float* __restrict__ means, const float* __restrict__ s
         tiles_touched[r] = rec.tiles;
         depth_key[r] = rec.key;
         rect[r] = make_uint2(rec.rx, rec.ry);
-        if (!vis) return;
+        if (!vis || !geom) return;
 #pragma unroll
         for (int q = 0; q < 4; ++q) geom[4 * r + q] = rec.geom[q];
         if (DEG >= 0) {
@@ -383,7 +383,7 @@ k_preprocess(int N, const float* __restrict__ means, const float* __restrict__ s
     for (int i = 0; i < 4; ++i) {
         const int j = i * 256 + tid, pp = j >> 2, q = j & 3;
         const int vv = pp >> lng, gl = pp & ((1 << lng) - 1), s = (gl << lv) + vv, gg = G0 + gl;
-        if (gg < N && sm.tiles[s] != 0u) geom[4 * ((size_t)vv * N + gg) + q] = sm.geom[q][s];
+        if (geom && gg < N && sm.tiles[s] != 0u) geom[4 * ((size_t)vv * N + gg) + q] = sm.geom[q][s];
     }
     if (DEG >= 0) {
 #pragma unroll
@@ -439,8 +439,10 @@ k_preprocess_views(int N, const float* __restrict__ means, const float* __restri
         tiles_touched[r] = rec.tiles;
         depth_key[r] = rec.key;
         rect[r] = make_uint2(rec.rx, rec.ry);
-        if (vis) {
-            any = true;
+        any |= vis;
+        // without geom (capacity planning) neither the record is stored nor,
+        // past the rectangle, formed
+        if (vis && geom) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) geom[4 * r + q] = rec.geom[q];
             if (DEG >= 0) {

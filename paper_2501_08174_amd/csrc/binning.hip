@@ -25,7 +25,7 @@ namespace sr {
 namespace {
 
 constexpr int kNT = 256;            // threads per block
-constexpr int kTile = kNT * 32;     // block chunks are multiples of the largest radix sub-tile
+constexpr int kTile = kNT * 32;     // elements per block of a radix pass over many elements
 constexpr int kMaxDigitBits = 9;    // radix digits of up to 9 bits (512 buckets)
 constexpr int kMaxRadix = 1 << kMaxDigitBits;
 
@@ -67,9 +67,10 @@ __device__ __forceinline__ void static_chunk(uint64_t n, int G, uint64_t* begin,
     *end = e < n ? e : n;
 }
 
-__device__ __forceinline__ void radix_chunk(uint32_t n, int G, uint32_t* begin, uint32_t* end) {
+// Chunks of whole sub-tiles of a radix pass.
+__device__ __forceinline__ void radix_chunk(uint32_t n, int G, uint32_t sub, uint32_t* begin, uint32_t* end) {
     uint32_t chunk = (n + G - 1) / G;
-    chunk = (chunk + kTile - 1) / kTile * kTile;
+    chunk = (chunk + sub - 1) / sub * sub;
     uint64_t b = (uint64_t)blockIdx.x * chunk;
     uint64_t e = b + chunk;
     *begin = (uint32_t)(b < n ? b : n);
@@ -158,14 +159,14 @@ k_vis_compact(uint64_t VN, int G, const uint32_t* __restrict__ tiles_touched,
 // ---- stable LSD radix sort of (u32 key, u32 value), count in device memory --
 
 __global__ void __launch_bounds__(kNT)
-k_radix_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ count, int G, int shift, int bits,
-             uint32_t* __restrict__ hist) {
+k_radix_hist(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ count, int G, int sub, int shift,
+             int bits, uint32_t* __restrict__ hist) {
     __shared__ uint32_t s_h[4][kMaxRadix];
     const int R = 1 << bits, w = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < 4 * kMaxRadix; i += kNT) (&s_h[0][0])[i] = 0;
     __syncthreads();
     uint32_t b, e;
-    radix_chunk(*count, G, &b, &e);
+    radix_chunk(*count, G, (uint32_t)sub, &b, &e);
     const uint32_t mask = (uint32_t)R - 1u;
     const int lane = __lane_id();
     // eight independent loads in flight per thread; a digit held by many
@@ -240,7 +241,7 @@ k_radix_scatter(const uint32_t* __restrict__ keys_in, const uint32_t* __restrict
     const int tid = threadIdx.x, lane = __lane_id(), w = tid >> 6;
     const int d0 = 2 * tid, d1 = 2 * tid + 1;
     uint32_t b, e;
-    radix_chunk(*count, G, &b, &e);
+    radix_chunk(*count, G, (uint32_t)(kNT * IPT), &b, &e);
     // global start of every digit for this block
     {
         const uint32_t t0 = d0 < R ? tot[d0] : 0u, t1 = d1 < R ? tot[d1] : 0u;
@@ -422,18 +423,23 @@ k_inst_offsets(const uint32_t* __restrict__ counters, int G, const uint32_t* __r
     }
 }
 
-constexpr int kEmitPerBlock = 4096;   // instances written per block
+// Instances written per block of the emission: a block works through its
+// windows of 256 pairs one after the other (~3 us each), so up to 16M
+// instances take small blocks (1.1M instances: 23 us with 4096, 8 us with
+// 1024; 5.6M: 36 and 32); beyond, the chip is full and larger ones read fewer pairs twice.
+constexpr int kEmitSmall = 1024, kEmitLarge = 4096;
+inline int emit_per_block(uint64_t cap) { return cap <= (16u << 20) ? kEmitSmall : kEmitLarge; }
 
 // First visible pair of every emission block: the last pair whose first
 // instance is at or before the block's first output position (one thread per
 // block, binary search over the instance offsets).
 __global__ void __launch_bounds__(kNT)
 k_emit_starts(const uint32_t* __restrict__ counters, const uint64_t* __restrict__ offs, uint32_t blocks,
-              uint32_t* __restrict__ starts) {
+              uint32_t per_block, uint32_t* __restrict__ starts) {
     const uint32_t b = blockIdx.x * kNT + threadIdx.x;
     if (b >= blocks) return;
     const uint32_t n_vis = counters[0];
-    const uint64_t ob = (uint64_t)b * kEmitPerBlock;
+    const uint64_t ob = (uint64_t)b * per_block;
     uint32_t lo = 0, hi = n_vis == 0 ? 0 : n_vis - 1;
     while (lo < hi) {
         const uint32_t mid = (lo + hi + 1) >> 1;
@@ -443,15 +449,15 @@ k_emit_starts(const uint32_t* __restrict__ counters, const uint64_t* __restrict_
 }
 
 // Emits the instances in depth order.  The output space is partitioned:
-// block b writes instances [b*4096, (b+1)*4096), whatever the number of
+// block b writes instances [b per_block, (b + 1) per_block), whatever the number of
 // surfels they come from, so surfels covering thousands of tiles (close to
 // a camera, first in depth order) do not serialise on a few blocks.
 __global__ void __launch_bounds__(kNT)
 k_emit(const uint32_t* __restrict__ counters, const uint64_t* __restrict__ total64, int N, int tsx, int tsy,
        const sr_camera* __restrict__ cams, const uint32_t* __restrict__ vis_vals,
        const ushort4* __restrict__ rect_sorted,
-       const uint64_t* __restrict__ offs, const uint32_t* __restrict__ starts, uint32_t* __restrict__ inst_keys,
-       uint32_t* __restrict__ inst_vals) {
+       const uint64_t* __restrict__ offs, const uint32_t* __restrict__ starts, uint32_t per_block,
+       uint32_t* __restrict__ inst_keys, uint32_t* __restrict__ inst_vals) {
     constexpr int GS = SR_TILE_GROUP;
     __shared__ uint64_t s_off[kNT];
     __shared__ uint32_t s_g[kNT];
@@ -461,9 +467,9 @@ k_emit(const uint32_t* __restrict__ counters, const uint64_t* __restrict__ total
     __shared__ uint2 s_rc[kNT];     // tile rectangle relative to the first group's first tile (x_lo | x_hi << 16, ...)
     __shared__ uint32_t s_first;
     const uint64_t stored = counters[2];          // min(instances, capacity)
-    const uint64_t ob = (uint64_t)blockIdx.x * kEmitPerBlock;
+    const uint64_t ob = (uint64_t)blockIdx.x * per_block;
     if (ob >= stored) return;
-    const uint64_t oe = ob + kEmitPerBlock < stored ? ob + kEmitPerBlock : stored;
+    const uint64_t oe = ob + per_block < stored ? ob + per_block : stored;
     const uint32_t n_vis = counters[0];
     const uint64_t total = *total64;
     if (threadIdx.x == 0) s_first = starts[blockIdx.x];
@@ -542,16 +548,17 @@ k_ranges_search(const uint32_t* __restrict__ counters, const uint32_t* __restric
     const int ty = local / c.tiles_x, tx = local - ty * c.tiles_x;
     const int t = c.group_offset + (ty / GS) * c.groups_x + tx / GS;
     const uint32_t n = counters[2];
-    uint32_t lo = 0, hi = n;
-    while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (keys[mid] < (uint32_t)t) lo = mid + 1; else hi = mid;
-    }
-    const uint32_t s = lo;
-    hi = n;
-    while (lo < hi) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (keys[mid] <= (uint32_t)t) lo = mid + 1; else hi = mid;
+    // both bounds at once: the searches' loads do not wait for each other
+    uint32_t s = 0, sh = n, lo = 0, hi = n;
+    while (s < sh || lo < hi) {
+        const uint32_t m0 = s + ((sh - s) >> 1), m1 = lo + ((hi - lo) >> 1);
+        const uint32_t k0 = keys[m0 < n ? m0 : 0u], k1 = keys[m1 < n ? m1 : 0u];
+        if (s < sh) {
+            if (k0 < (uint32_t)t) s = m0 + 1; else sh = m0;
+        }
+        if (lo < hi) {
+            if (k1 <= (uint32_t)t) lo = m1 + 1; else hi = m1;
+        }
     }
     ranges[tile] = s < lo ? make_uint2(s, lo) : make_uint2(0u, 0u);
 }
@@ -565,14 +572,42 @@ __global__ void k_copy_u32(const uint32_t* __restrict__ count, const uint32_t* _
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Blocks of a radix pass: one sub-tile each for small inputs, at most 4096
-// (16 per CU) for large ones; the digit histogram is 256 x G counters.
 constexpr int kMaxRadixBlocks = 4096;
-int grid_for(uint64_t elems) {
-    uint64_t g = (elems + kTile - 1) / kTile;
+int blocks_for(uint64_t elems, uint64_t per_block) {
+    uint64_t g = (elems + per_block - 1) / per_block;
     if (g < 1) g = 1;
     if (g > kMaxRadixBlocks) g = kMaxRadixBlocks;
     return (int)g;
+}
+
+// Blocks of the passes over the (view, surfel) pairs: 1024 pairs each (at
+// most 4096 blocks, 16 per CU): chunks of 8192 left a single view of 100,000
+// surfels 13 blocks (compaction 22 us, offsets 23 us; 5 us each now).
+int grid_pairs(uint64_t VN) { return blocks_for(VN, 1024); }
+
+// A radix pass: elements per thread of a sub-tile and blocks.  A block works
+// through its sub-tiles one after the other (5 to 6 us each), so few elements
+// take one small sub-tile per block: 1024 up to 256k elements, 2048 up to 2M
+// (100,000 pairs: 24.5 us a pass with four sub-tiles of 2048 per block, 6.5 us
+// with one of 1024; 2M pairs: 28 us, 15.6 us with one of 2048).  Beyond, the
+// chip is full: 8192 elements a block in sub-tiles of the caller's measured
+// size (many), so that the digit histogram stays small (5.6M instances, 37 us:
+// one sub-tile of 2048 per block measured 41).
+struct RadixGrid {
+    int ipt, blocks;
+};
+RadixGrid radix_grid(uint64_t elems, int many) {
+    if (elems <= (1u << 18)) return {4, blocks_for(elems, kNT * 4)};
+    if (elems <= (1u << 21)) return {8, blocks_for(elems, kNT * 8)};
+    return {many, blocks_for(elems, kTile)};
+}
+
+void radix_pass(const RadixGrid& g, const uint32_t* sk, const uint32_t* sv, const uint32_t* count, int shift, int bits,
+                uint32_t* hist, uint32_t* tot, uint32_t* dk, uint32_t* dv, hipStream_t s) {
+    hipLaunchKernelGGL(k_radix_hist, dim3(g.blocks), dim3(kNT), 0, s, sk, count, g.blocks, kNT * g.ipt, shift, bits, hist);
+    hipLaunchKernelGGL(k_radix_digit_scan, dim3(1 << bits), dim3(kNT), 0, s, hist, g.blocks, tot);
+    auto scatter = g.ipt == 4 ? k_radix_scatter<4> : (g.ipt == 8 ? k_radix_scatter<8> : k_radix_scatter<16>);
+    hipLaunchKernelGGL(scatter, dim3(g.blocks), dim3(kNT), 0, s, sk, sv, count, g.blocks, shift, bits, hist, tot, dk, dv);
 }
 
 struct BinWs {
@@ -603,7 +638,7 @@ BinWs carve(void* base, uint64_t VN, uint64_t cap) {
     w.ioff = (uint64_t*)take(VN * 8);
     w.tts = (uint32_t*)take(VN * 4);
     w.rsort = (ushort4*)take(VN * 8);
-    w.estart = (uint32_t*)take(((cap + kEmitPerBlock - 1) / kEmitPerBlock) * 4);
+    w.estart = (uint32_t*)take(((cap + emit_per_block(cap) - 1) / emit_per_block(cap)) * 4);
     w.itotal = (uint64_t*)take(8);
     w.bytes = off;
     return w;
@@ -615,7 +650,8 @@ BinWs carve(void* base, uint64_t VN, uint64_t cap) {
 uint32_t* radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uint32_t* vals_dst,
                      const uint32_t* count, uint64_t cap, int nbits, uint32_t* hist, uint32_t* tot,
                      hipStream_t s) {
-    const int G = grid_for(cap);
+    // many: sub-tiles of 4096 (a sweep over 2048..8192 per pass: the fastest)
+    const RadixGrid G = radix_grid(cap, 16);
     const int passes = (nbits + kMaxDigitBits - 1) / kMaxDigitBits;
     if (passes == 0) {
         hipLaunchKernelGGL(k_copy_u32, dim3(1024), dim3(256), 0, s, count, v0, vals_dst);
@@ -631,11 +667,7 @@ uint32_t* radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1, uin
         const bool last = p == passes - 1;
         uint32_t* dk = sk == k0 ? k1 : k0;
         uint32_t* dv = last ? vals_dst : (sv == v0 ? v1 : v0);
-        hipLaunchKernelGGL(k_radix_hist, dim3(G), dim3(kNT), 0, s, sk, count, G, shift, bits, hist);
-        hipLaunchKernelGGL(k_radix_digit_scan, dim3(1 << bits), dim3(kNT), 0, s, hist, G, tot);
-        // sub-tiles of 4096 (a sweep over 2048..8192 per pass: the fastest)
-        hipLaunchKernelGGL(k_radix_scatter<16>, dim3(G), dim3(kNT), 0, s, sk, sv, count, G, shift, bits, hist, tot,
-                           dk, dv);
+        radix_pass(G, sk, sv, count, shift, bits, hist, tot, dk, dv, s);
         sk = dk;
         sv = dv;
         shift += bits;
@@ -661,10 +693,13 @@ hipError_t launch_bin_and_sort(const sr_config& cfg, int N, int V, int total_til
     if ((1 << gsx) != SR_TILE_GROUP * cfg.tile_w || (1 << gsy) != SR_TILE_GROUP * cfg.tile_h)
         return hipErrorInvalidValue;
     BinWs w = carve(workspace, VN, cap);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, s, counters, 0u, (uint64_t)SR_COUNTERS);
-    hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, s, ranges, 0u, 2ull * (uint64_t)total_tiles);
+    // the counters are all written by the scans, the ranges by the search
+    static_assert(SR_COUNTERS == 4, "counters the scans write");
+    if (VN == 0) hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(256), 0, s, counters, 0u, (uint64_t)SR_COUNTERS);
+    if ((VN == 0 || count_only) && total_tiles > 0)
+        hipLaunchKernelGGL(k_fill_u32, dim3(1024), dim3(256), 0, s, ranges, 0u, 2ull * (uint64_t)total_tiles);
     if (VN == 0) return hipGetLastError();
-    const int Gv = grid_for(VN);
+    const int Gv = grid_pairs(VN);
     if (count_only) {
         // the counts are all that was asked for
         hipLaunchKernelGGL(k_plan_count, dim3(Gv), dim3(kNT), 0, s, VN, Gv, tiles_touched, (const ushort4*)rect, gsx, gsy,
@@ -681,16 +716,13 @@ hipError_t launch_bin_and_sort(const sr_config& cfg, int N, int V, int total_til
     // 2. stable sort by the 32 depth bits (ties keep (view, surfel) order):
     //    four 8-bit passes, the result ends in (vk0, vv0)
     {
-        const int G = grid_for(VN);
+        // many: sub-tiles of 2048 pairs (8 per digit on average): faster than
+        // 1024, 4096 or 8192 in a sweep on the 1M-surfel, 16-view batch
+        const RadixGrid G = radix_grid(VN, 8);
         uint32_t *sk = w.vk0, *sv = w.vv0, *dk = w.vk1, *dv = w.vv1;
         for (int p = 0; p < 4; ++p) {
-            hipLaunchKernelGGL(k_radix_hist, dim3(G), dim3(kNT), 0, s, sk, counters, G, 8 * p, 8, w.hist);
-            hipLaunchKernelGGL(k_radix_digit_scan, dim3(256), dim3(kNT), 0, s, w.hist, G, w.tot);
-            // sub-tiles of 2048 pairs (8 per digit on average): faster than
-            // 1024, 4096 or 8192 in a sweep on the 1M-surfel, 16-view batch
             // the sorted depth keys themselves are not used after the last pass
-            hipLaunchKernelGGL(k_radix_scatter<8>, dim3(G), dim3(kNT), 0, s, sk, sv, counters, G, 8 * p, 8, w.hist,
-                               w.tot, p == 3 ? nullptr : dk, dv);
+            radix_pass(G, sk, sv, counters, 8 * p, 8, w.hist, w.tot, p == 3 ? nullptr : dk, dv, s);
             uint32_t* t;
             t = sk; sk = dk; dk = t;
             t = sv; sv = dv; dv = t;
@@ -703,12 +735,14 @@ hipError_t launch_bin_and_sort(const sr_config& cfg, int N, int V, int total_til
                        w.tts, w.rsort, w.isum);
     hipLaunchKernelGGL(k_scan_small<uint64_t>, dim3(1), dim3(kNT), 0, s, w.isum, Gi, counters, 1, cap, w.itotal, status);
     hipLaunchKernelGGL(k_inst_offsets, dim3(Gi), dim3(kNT), 0, s, counters, Gi, w.tts, w.isum, w.ioff);
-    const uint64_t emit_blocks = ((uint64_t)cap + kEmitPerBlock - 1) / kEmitPerBlock;
+    const uint32_t per_block = (uint32_t)emit_per_block(cap);
+    const uint64_t emit_blocks = ((uint64_t)cap + per_block - 1) / per_block;
     if (emit_blocks > 0) {
         hipLaunchKernelGGL(k_emit_starts, dim3((unsigned)((emit_blocks + kNT - 1) / kNT)), dim3(kNT), 0, s, counters,
-                           w.ioff, (uint32_t)emit_blocks, w.estart);
+                           w.ioff, (uint32_t)emit_blocks, per_block, w.estart);
         hipLaunchKernelGGL(k_emit, dim3((unsigned)emit_blocks), dim3(kNT), 0, s, counters, w.itotal, N,
-                           gsx - 2, gsy - 2, cams_dev, w.vv0, (const ushort4*)w.rsort, w.ioff, w.estart, w.ik0, w.iv0);
+                           gsx - 2, gsy - 2, cams_dev, w.vv0, (const ushort4*)w.rsort, w.ioff, w.estart,
+                           per_block, w.ik0, w.iv0);
     }
     // 4. stable sort by group id; values land in the caller's array
     int nbits = 0;
@@ -790,7 +824,7 @@ struct OrderWs {
 };
 
 size_t order_ws_layout(int T, void* base, OrderWs* w) {
-    const uint64_t G = (uint64_t)grid_for((uint64_t)T);
+    const uint64_t G = (uint64_t)radix_grid((uint64_t)T, 16).blocks;
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) -> uint32_t* {
         uint32_t* p = base ? (uint32_t*)((char*)base + off) : nullptr;

@@ -70,9 +70,14 @@ k_loss_partial(const sr_camera* __restrict__ cams, int V, const float* __restric
     }
 }
 
+// The total of a single view, written with its terms (one launch less).
+__device__ __forceinline__ void one_view_total(float a, float wa, float b, float wb, float* __restrict__ loss) {
+    loss[2] = wa * a + wb * b;
+}
+
 __global__ void __launch_bounds__(kNT)
-k_loss_final(const sr_camera* __restrict__ cams, int V, int nchunk, const float* __restrict__ partial,
-             float* __restrict__ loss) {
+k_loss_final(const sr_camera* __restrict__ cams, int V, int nchunk, const float* __restrict__ partial, float gamma,
+             float w_c, float* __restrict__ loss) {
     __shared__ float s[kNT];
     const int v = blockIdx.x;
     float lb = 0.f, l1 = 0.f;
@@ -86,6 +91,7 @@ k_loss_final(const sr_camera* __restrict__ cams, int V, int nchunk, const float*
         const float HW = (float)cams[v].width * (float)cams[v].height;
         loss[v] = lb / HW;
         loss[V + v] = l1 / (3.0f * HW);
+        if (V == 1) one_view_total(loss[1], w_c, loss[0], gamma, loss);
     }
 }
 
@@ -102,7 +108,7 @@ k_loss_total(int V, float gamma, float w_c, float* __restrict__ loss) {
 // Per-view totals from the per-tile partial sums of the fused training step
 // (tiles of a view are contiguous), summed in tile order.
 __global__ void __launch_bounds__(kNT)
-k_loss_tiles(const sr_camera* __restrict__ cams, int V, const float* __restrict__ tile_loss,
+k_loss_tiles(const sr_camera* __restrict__ cams, int V, const float* __restrict__ tile_loss, float gamma, float w_c,
              float* __restrict__ loss) {
     __shared__ float s[kNT];
     const int v = blockIdx.x;
@@ -119,6 +125,7 @@ k_loss_tiles(const sr_camera* __restrict__ cams, int V, const float* __restrict_
         const float HW = (float)c.width * (float)c.height;
         loss[v] = lb / HW;
         loss[V + v] = l1 / (3.0f * HW);
+        if (V == 1) one_view_total(loss[1], w_c, loss[0], gamma, loss);
     }
 }
 
@@ -283,8 +290,8 @@ k_reg_partial(const sr_camera* __restrict__ cams, int V, const float* __restrict
 
 // loss[v] = L_d,v, loss[V+v] = L_n,v from the chunk partials; loss[2V] total
 __global__ void __launch_bounds__(kNT)
-k_reg_final(const sr_camera* __restrict__ cams, int V, int nslot, const float* __restrict__ partial,
-            float* __restrict__ loss) {
+k_reg_final(const sr_camera* __restrict__ cams, int V, int nslot, const float* __restrict__ partial, float w_dist,
+            float w_normal, float* __restrict__ loss) {
     __shared__ float s[kNT];
     const int v = blockIdx.x;
     const int nt = reg_tiles(cams[v].width, cams[v].height);
@@ -299,6 +306,7 @@ k_reg_final(const sr_camera* __restrict__ cams, int V, int nslot, const float* _
         const float HW = (float)cams[v].width * (float)cams[v].height;
         loss[v] = ld / HW;
         loss[V + v] = ln / HW;
+        if (V == 1) one_view_total(loss[0], w_dist, loss[1], w_normal, loss);
     }
 }
 
@@ -324,16 +332,17 @@ hipError_t launch_reg_loss(int V, int max_tiles, int total_tiles, const sr_camer
     hipLaunchKernelGGL(k_reg_partial, dim3(total_tiles), dim3(kNT), 0, s, cams, V, alpha, depth, normal, dist,
                        median, w_dist, w_normal, max_tiles, (float*)ws, dL_dalpha, dL_ddepth, dL_dnormal, dL_ddist,
                        dL_dmedian);
-    hipLaunchKernelGGL(k_reg_final, dim3(V), dim3(kNT), 0, s, cams, V, max_tiles, (const float*)ws, loss);
-    hipLaunchKernelGGL(k_reg_total, dim3(1), dim3(kNT), 0, s, V, w_dist, w_normal, loss);
+    hipLaunchKernelGGL(k_reg_final, dim3(V), dim3(kNT), 0, s, cams, V, max_tiles, (const float*)ws, w_dist,
+                       w_normal, loss);
+    if (V > 1) hipLaunchKernelGGL(k_reg_total, dim3(1), dim3(kNT), 0, s, V, w_dist, w_normal, loss);
     return hipGetLastError();
 }
 
 hipError_t launch_loss_from_tiles(int V, const sr_camera* cams, const float* tile_loss, float gamma, float w_c,
                                   float* loss, hipStream_t s) {
     if (V == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_loss_tiles, dim3(V), dim3(kNT), 0, s, cams, V, tile_loss, loss);
-    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(kNT), 0, s, V, gamma, w_c, loss);
+    hipLaunchKernelGGL(k_loss_tiles, dim3(V), dim3(kNT), 0, s, cams, V, tile_loss, gamma, w_c, loss);
+    if (V > 1) hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(kNT), 0, s, V, gamma, w_c, loss);
     return hipGetLastError();
 }
 
@@ -351,8 +360,10 @@ hipError_t launch_loss(int V, int64_t max_hw, const sr_camera* cams, const float
     const int nchunk = loss_chunks(max_hw);
     hipLaunchKernelGGL(k_loss_partial, dim3(nchunk, V), dim3(kNT), 0, s, cams, V, alpha, mask, color, target, gamma,
                        w_c, nchunk, (float*)ws, dL_dalpha, dL_dcolor);
-    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(kNT), 0, s, cams, V, nchunk, (const float*)ws, loss);
-    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(kNT), 0, s, V, gamma, color ? w_c : 0.f, loss);
+    hipLaunchKernelGGL(k_loss_final, dim3(V), dim3(kNT), 0, s, cams, V, nchunk, (const float*)ws, gamma,
+                       color ? w_c : 0.f, loss);
+    if (V > 1)
+        hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(kNT), 0, s, V, gamma, color ? w_c : 0.f, loss);
     return hipGetLastError();
 }
 

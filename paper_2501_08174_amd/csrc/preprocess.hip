@@ -410,7 +410,7 @@ k_preprocess_views(int N, const float* __restrict__ means, const float* __restri
                    int tile_wl, int tile_hl, int V, const sr_camera* __restrict__ cams,
                    float4* __restrict__ geom, float4* __restrict__ app, uint2* __restrict__ rect,
                    uint32_t* __restrict__ tiles_touched, uint32_t* __restrict__ depth_key,
-                   uint8_t* __restrict__ in_frustum) {
+                   uint8_t* __restrict__ in_frustum, bool accumulate) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= N) return;
     SurfelTerms s;
@@ -451,7 +451,8 @@ k_preprocess_views(int N, const float* __restrict__ means, const float* __restri
             }
         }
     }
-    if (any && in_frustum) in_frustum[g] = 1;
+    // this thread is the only writer: no clearing pass before it
+    if (in_frustum && (any || !accumulate)) in_frustum[g] = any ? 1 : 0;
 }
 
 __global__ void k_zero_u8(uint8_t* __restrict__ p, int n) {
@@ -707,7 +708,9 @@ hipError_t launch_preprocess(const sr_config& cfg, int N, const float* means, co
     if (N == 0) return hipSuccess;
     // the supported tile shapes are powers of two
     if ((cfg.tile_w & (cfg.tile_w - 1)) != 0 || (cfg.tile_h & (cfg.tile_h - 1)) != 0) return hipErrorInvalidValue;
-    if (in_frustum && !(cfg.flags & SR_FLAG_ACCUMULATE))
+    const bool accumulate = (cfg.flags & SR_FLAG_ACCUMULATE) != 0;
+    const bool per_surfel = N >= kPreprocessLoopMinSurfels || V == 1;
+    if (in_frustum && !accumulate && (!per_surfel || V == 0))
         hipLaunchKernelGGL(k_zero_u8, dim3((N + 255) / 256), dim3(256), 0, stream, in_frustum, N);
     const uint64_t threads = (uint64_t)N * (uint64_t)V;
     if (threads == 0) return hipGetLastError();
@@ -717,14 +720,14 @@ hipError_t launch_preprocess(const sr_config& cfg, int N, const float* means, co
     // thread per surfel looping over the views; else one thread per (surfel,
     // view), with staged writes when V divides the workgroup size (V a power
     // of two <= 256)
-    const bool per_surfel = N >= kPreprocessLoopMinSurfels || V == 1;
     const int twl = __builtin_ctz((unsigned)cfg.tile_w), thl = __builtin_ctz((unsigned)cfg.tile_h);
     const bool staged = V <= 256 && (256 % V) == 0;
 #define SR_PRE(D)                                                                                                 \
     if (per_surfel)                                                                                               \
         hipLaunchKernelGGL((k_preprocess_views<D>), dim3((N + 255) / 256), block, 0, stream, N, means, scales,    \
                            quats, opac, sh, cfg.sh_stride, cfg.alpha_min, twl, thl, V, cams_dev,                  \
-                           (float4*)geom, (float4*)app, (uint2*)rect, tiles_touched, depth_key, in_frustum);      \
+                           (float4*)geom, (float4*)app, (uint2*)rect, tiles_touched, depth_key, in_frustum,       \
+                           accumulate);                                                                           \
     else if (staged)                                                                                              \
         hipLaunchKernelGGL((k_preprocess<D, true>), grid, block, 0, stream, N, means, scales, quats, opac, sh,    \
                            cfg.sh_stride, cfg.alpha_min, twl, thl, V, cams_dev, (float4*)geom,                    \

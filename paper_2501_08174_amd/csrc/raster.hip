@@ -107,7 +107,7 @@ constexpr int kMaxWaves = 8;    // waves per workgroup (tiles of up to 512 pixel
 // one 800x600 view; the pruning pass of 100 views 50.5 / 50.5 / 49.7 ms.  With
 // records in LDS (few tiles) four and five measure the same.
 #define SR_OCCUPANCY(waves) __attribute__((amdgpu_waves_per_eu(waves)))
-constexpr int kFwdWaves = 6, kPruneWaves = 7, kBwdWaves = 5, kTrainWaves = 6, kLdsWaves = 5;
+constexpr int kFwdWaves = 6, kPruneWaves = 7, kBwdWaves = 5, kTrainWaves = 6, kLdsWaves = 5, kAheadWaves = 4;
 
 // MODE bits: 1 shade (colour, depth, normal, distortion outputs), 2 occlusion
 // statistics, 4 count reached/blended pairs (work accounting), 8 median depth
@@ -283,16 +283,29 @@ __device__ __forceinline__ void load_scalar(const float4* __restrict__ geom_v, c
     }
 }
 
-template <bool APP, typename Stage>
-__device__ __forceinline__ void load_lds(const Stage& st, int k, EntryRec& r) {
+// The parts of a staged record that eval_test reads, and the rest.
+template <typename Stage>
+__device__ __forceinline__ void load_lds_test(const Stage& st, int k, EntryRec& r) {
 #pragma unroll
-    for (int q = 0; q < kGeomF4; ++q) {
+    for (int q = 0; q < 2; ++q) {
         const float4 v = st.g[q][k];
         r.g[4 * q] = v.x;
         r.g[4 * q + 1] = v.y;
         r.g[4 * q + 2] = v.z;
         r.g[4 * q + 3] = v.w;
     }
+    r.g[8] = st.g[2][k].x;
+    r.g[9] = st.g[2][k].y;
+    r.g[10] = st.g[2][k].z;
+    r.g[15] = st.g[3][k].w;
+}
+
+template <bool APP, typename Stage>
+__device__ __forceinline__ void load_lds_rest(const Stage& st, int k, EntryRec& r) {
+    r.g[11] = st.g[2][k].w;
+    r.g[12] = st.g[3][k].x;
+    r.g[13] = st.g[3][k].y;
+    r.g[14] = st.g[3][k].z;
     if (APP) {
         const float4 a0 = st.a[0][k];
         const float2 a1 = *reinterpret_cast<const float2*>(&st.a[1][k]);
@@ -520,6 +533,8 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
           if constexpr (SCALAR) {
             load_scalar<SHADE, SHADE>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
             next_rec.c = sm.rec.c[c * 64 + nbit];
+          } else {
+            load_lds_test(sm.rec, c * 64 + nbit, next_rec);
           }
           // HITS: this wave's blended pixels of entry c * 64 + lane
           uint32_t my_hits = 0;
@@ -528,13 +543,12 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
             EntryRec rec = next_rec;
             live &= live - 1ull;
             nbit = live != 0ull ? (int)__builtin_ctzll(live) : bit;
-            uint32_t jidx;                         // run position + 1
+            const uint32_t jidx = __builtin_amdgcn_readlane(my_pos, bit);    // run position + 1
             if constexpr (SCALAR) {
                 load_scalar<SHADE, SHADE>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
-                jidx = __builtin_amdgcn_readlane(my_pos, bit);
             } else {
-                load_lds<SHADE>(sm.rec, k, rec);
-                jidx = sm.pos[k];
+                load_lds_test(sm.rec, k, rec);
+                load_lds_rest<SHADE>(sm.rec, k, rec);
             }
             const SurfelGeom sg = geom_of<SCALAR>(rec);
             PairEval e;
@@ -905,6 +919,13 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
                                          const uint32_t* bitcache = nullptr) {
     static_assert(BATCH <= NT, "one record per thread and batch");
     static_assert(!(HITS && GEO), "the count is taken by the training step alone");
+    // The depth terms from LDS (few tiles, often less than a wave per SIMD): the
+    // next entry's test is read a whole entry ahead, for 4 waves per SIMD
+    // instead of 5.  56 tiles of 40,000 entries: k_render_bwd 12.7 -> 11.7 ms.
+    // The training step has no registers left for it (14.0 -> 14.2 ms on two
+    // 165x153 views of 700k surfels), nor has the forward anything to hide it
+    // behind (2M surfels, 1237x822: 0.554 -> 0.559 ms).
+    constexpr bool AHEAD = !SCALAR && GEO;
     const int tid = threadIdx.x;
     const int lane = __lane_id();
     __syncthreads();
@@ -980,6 +1001,8 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
           if constexpr (SCALAR) {
             load_scalar<true, GEO>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
             next_rec.c = sm.rec.c[c * 64 + nbit];
+          } else if constexpr (AHEAD) {
+            load_lds_test(sm.rec, c * 64 + nbit, next_rec);
           }
           uint32_t my_hits = 0;       // HITS: this wave's blended pixels of entry c * 64 + lane
           uint64_t blended = 0ull;    // the chunk's entries that a pixel of the wave blends
@@ -989,18 +1012,20 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
             live &= ~(1ull << hb);
             nbit = live != 0ull ? 63 - (int)__builtin_clzll(live) : hb;
             uint32_t jj;                           // run position
+            if constexpr (SCALAR || AHEAD) jj = __builtin_amdgcn_readlane(my_pos, hb);
+            else jj = sm.pos[k];
             if constexpr (SCALAR) {
                 load_scalar<true, GEO>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
-                jj = __builtin_amdgcn_readlane(my_pos, hb);
             } else {
-                load_lds<true>(sm.rec, k, rec);
-                jj = sm.pos[k];
+                if constexpr (!AHEAD) load_lds_test(sm.rec, k, rec);
+                load_lds_rest<true>(sm.rec, k, rec);
             }
             const SurfelGeom sg = geom_of<SCALAR>(rec);
             PairEval e;
             eval_test<SCALAR>(sg, px, py, e);
             // behind the last use of this entry's: the same registers
             if constexpr (SCALAR) next_rec.c = sm.rec.c[c * 64 + nbit];
+            else if constexpr (AHEAD) load_lds_test(sm.rec, c * 64 + nbit, next_rec);
             const uint64_t blm = ballot64(jj < pb.ncon) & pass_mask(e);
             if (blm == 0ull) continue;
             blended |= 1ull << hb;
@@ -1113,7 +1138,7 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
 }
 
 template <int TW, int TH, int BATCH, bool GEO, bool SCALAR>
-__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(kBwdWaves)
+__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(SCALAR ? kBwdWaves : GEO ? kAheadWaves : kLdsWaves)
 k_render_bwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __restrict__ geom,
              const float4* __restrict__ app, const uint32_t* __restrict__ vals, const uint2* __restrict__ ranges,
              RasterConsts rc, const float* __restrict__ alpha, const float* __restrict__ depth,

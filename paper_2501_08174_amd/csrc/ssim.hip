@@ -140,8 +140,9 @@ __device__ __forceinline__ bool ssim_tile(const sr_camera* cams, int V, SsimTile
 }
 
 // Calls f(k, inside, p) for this thread's values of the tile with halo: k is
-// the position in an LDS array, p the pixel (clamped to the image).  Unrolled:
-// every load of a pass over the values is issued before the first is used.
+// the position in an LDS array, p the pixel (clamped to the image; 64 bits, a
+// view may hold more than 2^31 pixels).  Unrolled: every load of a pass over
+// the values is issued before the first is used.
 constexpr int kLoads = (kHX * kHY + kNT - 1) / kNT;
 template <typename F>
 __device__ __forceinline__ void for_halo(const SsimTile& t, F&& f) {
@@ -151,7 +152,7 @@ __device__ __forceinline__ void for_halo(const SsimTile& t, F&& f) {
         const int ly = k / kHX, lx = k - ly * kHX;
         const int i = t.x0 - kR + lx, j = t.y0 - kR + ly;
         const bool in = k < kHX * kHY && i >= 0 && i < t.W && j >= 0 && j < t.H;
-        f(r, k < kHX * kHY ? ly * kSX + lx : -1, in, in ? j * t.W + i : 0);
+        f(r, k < kHX * kHY ? ly * kSX + lx : -1, in, in ? (int64_t)j * t.W + i : (int64_t)0);
     }
 }
 
@@ -161,12 +162,12 @@ __device__ __forceinline__ void load_xy(const SsimTile& t, const float* __restri
                                         float (&sy)[kHY][kSX]) {
     float xv[kLoads], yv[kLoads];
     uint8_t mv[kLoads];
-    for_halo(t, [&](int r, int, bool, int p) {
+    for_halo(t, [&](int r, int, bool, int64_t p) {
         xv[r] = C[p];
         yv[r] = I[p];
         mv[r] = M[p];
     });
-    for_halo(t, [&](int r, int k, bool in, int) {
+    for_halo(t, [&](int r, int k, bool in, int64_t) {
         const float m = mv[r] ? 1.0f : 0.0f;
         if (k >= 0) {
             (&sx[0][0])[k] = in ? m * xv[r] : 0.f;
@@ -267,12 +268,12 @@ k_ssim_bwd(const sr_camera* __restrict__ cams, int V, const float* __restrict__ 
     {
         const float* g = gmaps + base;
         float v[3][kLoads];
-        for_halo(t, [&](int r, int, bool, int p) {
+        for_halo(t, [&](int r, int, bool, int64_t p) {
             v[0][r] = g[p];
             v[1][r] = g[P3 + p];
             v[2][r] = g[2 * P3 + p];
         });
-        for_halo(t, [&](int r, int k, bool in, int) {
+        for_halo(t, [&](int r, int k, bool in, int64_t) {
 #pragma unroll
             for (int m = 0; m < 3; ++m)
                 if (k >= 0) (&sg[m][0][0])[k] = in ? v[m][r] : 0.f;

@@ -160,12 +160,26 @@ __device__ __forceinline__ float f3dot(float3 a, float3 b) {
     return a.x * b.x + a.y * b.y + a.z * b.z;
 }
 
-// n / d from inv = 1 / d: the product corrected by its remainder is the
+// n / d from inv = 1 / d, d > 0: the product corrected by its remainder is the
 // rounded quotient (Markstein), in four operations instead of a division's
-// ten.  Infinite operands have no remainder: the product is the quotient then.
-__device__ __forceinline__ float quotient(float n, float d, float inv) {
+// ten, where the reciprocal and the quotient are normal numbers (or the
+// quotient is zero).  ok is cleared where they are not: reciprocals of d below
+// 2.9e-39 overflow, those above 8.5e37 are subnormal, and infinities and NaNs
+// have no remainder.
+__device__ __forceinline__ float quotient(float n, float d, float inv, bool& ok) {
+    constexpr int kNormal = 0x108, kZero = 0x60;      // of either sign, as v_cmp_class counts them
     const float q = n * inv, c = __builtin_fmaf(__builtin_fmaf(-q, d, n), inv, q);
-    return c == c ? c : q;
+    ok = ok && __builtin_amdgcn_classf(inv, kNormal) && __builtin_amdgcn_classf(c, kNormal | kZero);
+    return c;
+}
+
+// The quotients of three numbers by d; the division itself, in a branch that
+// ordinary maps do not enter, where the above does not hold for one of them.
+__device__ __forceinline__ float3 quotient3(float3 n, float d, float inv) {
+    bool ok = true;
+    float3 c = make_float3(quotient(n.x, d, inv, ok), quotient(n.y, d, inv, ok), quotient(n.z, d, inv, ok));
+    if (!ok) c = make_float3(n.x / d, n.y / d, n.z / d);
+    return c;
 }
 
 __host__ __device__ inline int reg_tiles_of(int W, int H) {
@@ -274,12 +288,11 @@ k_reg_partial(const sr_camera* __restrict__ cams, int V, const float* __restrict
             const float len = sqrtf(f3dot(n, n));
             const bool some = len > kEpsNormal;
             const float den = some ? len : kEpsNormal, inv = 1.0f / den;
-            nd = make_float3(quotient(n.x, den, inv), quotient(n.y, den, inv), quotient(n.z, den, inv));
+            nd = quotient3(n, den, inv);
             const float3 g = make_float3(-gn * ld_n[r].x, -gn * ld_n[r].y, -gn * ld_n[r].z);
             // dL/dn: the part across nd, or all of g where the length is the constant
             const float kk = some ? f3dot(nd, g) : 0.f;
-            const float3 dn = make_float3(quotient(g.x - nd.x * kk, den, inv), quotient(g.y - nd.y * kk, den, inv),
-                                          quotient(g.z - nd.z * kk, den, inv));
+            const float3 dn = quotient3(make_float3(g.x - nd.x * kk, g.y - nd.y * kk, g.z - nd.z * kk), den, inv);
             ga = f3cross(b, dn);                             // dL/da
             gb = f3cross(dn, a);                             // dL/db
         }
@@ -312,9 +325,15 @@ k_reg_partial(const sr_camera* __restrict__ cams, int V, const float* __restrict
         if (Md) {
             dL_dmedian[o1] = ds;
         } else if (a > 0.f) {
-            const float inv = 1.0f / a;
-            gD = quotient(ds, a, inv);
-            gA = gA - quotient(ds * sP[ly + 2][lx + 2].z, a, inv);    // the point's z is D / A
+            const float inv = 1.0f / a, dz = ds * sP[ly + 2][lx + 2].z;      // the point's z is D / A
+            bool ok = true;
+            gD = quotient(ds, a, inv, ok);
+            float gz = quotient(dz, a, inv, ok);
+            if (!ok) {
+                gD = ds / a;
+                gz = dz / a;
+            }
+            gA = gA - gz;
         }
         dL_dalpha[o1] = px_ga[q] + gA;
         dL_ddepth[o1] = gD;

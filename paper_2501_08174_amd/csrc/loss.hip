@@ -290,9 +290,11 @@ k_reg_partial(const sr_camera* __restrict__ cams, int V, const float* __restrict
             const float den = some ? len : kEpsNormal, inv = 1.0f / den;
             nd = quotient3(n, den, inv);
             const float3 g = make_float3(-gn * ld_n[r].x, -gn * ld_n[r].y, -gn * ld_n[r].z);
-            // dL/dn: the part across nd, or all of g where the length is the constant
-            const float kk = some ? f3dot(nd, g) : 0.f;
-            const float3 dn = quotient3(make_float3(g.x - nd.x * kk, g.y - nd.y * kk, g.z - nd.z * kk), den, inv);
+            // dL/dn: the part across nd, or all of g where the length is the
+            // constant (also that of a NaN normal, whose nd stays out of it)
+            const float kk = f3dot(nd, g);
+            const float3 along = some ? make_float3(nd.x * kk, nd.y * kk, nd.z * kk) : make_float3(0.f, 0.f, 0.f);
+            const float3 dn = quotient3(f3sub(g, along), den, inv);
             ga = f3cross(b, dn);                             // dL/da
             gb = f3cross(dn, a);                             // dL/db
         }

@@ -1,5 +1,6 @@
 """The 2DGS regularisers' gradients for values at the ends of the range:
-quotients by alphas whose reciprocal overflows."""
+quotients by alphas whose reciprocal overflows, and depths that are not
+numbers."""
 import numpy as np
 import pytest
 import torch
@@ -63,3 +64,20 @@ def test_zero_gradient_of_any_alpha(a):
     gA, gD, _, _ = _grads(alpha, alpha * torch.tensor(z, device="cuda"), torch.zeros_like(normal))
     assert not gD.any()
     np.testing.assert_array_equal(gA, np.float32(W_NORMAL) * (np.float32(1) / np.float32(W * H)))
+
+
+@pytest.mark.parametrize("of", ["depth", "median"])
+def test_depth_that_is_no_number(of):
+    """A NaN depth makes the two tangent vectors that it takes part in NaN, and
+    with them the points of the other tangent of those normals: the four
+    diagonal neighbours.  The points two pixels away are passed vectors of the
+    finite tangent alone."""
+    _, z, normal = _maps(3)
+    x, y = 30, 20
+    one, bad = torch.ones(W * H, device="cuda"), torch.tensor(z, device="cuda")
+    bad[y * W + x] = float("nan")
+    grads = _grads(one, bad, normal) if of == "depth" else _grads(one, one, normal, bad)
+    got = ~np.isfinite(grads[1 if of == "depth" else 4].reshape(H, W))
+    want = np.zeros_like(got)
+    want[[y - 1, y - 1, y + 1, y + 1], [x - 1, x + 1, x - 1, x + 1]] = True
+    np.testing.assert_array_equal(got, want)

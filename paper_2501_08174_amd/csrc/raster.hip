@@ -373,7 +373,6 @@ template <int NT, int BATCH, bool GEO, bool HITS, bool SCALAR>
 struct BwdSmem {
     static constexpr int kAcc = GEO ? 23 : 17;
     RecStage<SCALAR, BATCH, true> rec;
-    float2 mid[BATCH];            // the tile's middle relative to the projected centre
     uint32_t id[BATCH];           // surfel id | wave bits << SR_INST_ID_BITS
     uint32_t pos[BATCH];          // run position
     float4 xp[NT];                // transposition scratch, 64 slots per wave
@@ -780,20 +779,20 @@ __device__ __forceinline__ void pix_bwd_init(PixBwd& pb, const TileCtx& t, float
 // values, b = lane >> 2 is its column of pixels 16 t + b (t = 0..3) of the
 // wave's 8x8 block, i.e. x = b % 8, y = 2 t + b / 8.
 struct ContractLane {
-    float x, y;         // of the column's middle, relative to the tile's
+    float x, y;         // image coordinates of the column and of its first pixel (t = 0)
     int slot;           // of the accumulator this lane adds to, or -1
     int slot6;          // the same for wave_sum6, from slot 16 on
 };
 
-template <int TW, int TH>
-__device__ __forceinline__ ContractLane contract_lane() {
+template <int TW>
+__device__ __forceinline__ ContractLane contract_lane(const TileCtx& t) {
     constexpr int WB = kWaveBlock;
     const int lane = __lane_id(), b = lane >> 2, row = lane >> 4;
     const int w = wave_index();
     const int bx = (w % (TW / WB)) * WB, by = (w / (TW / WB)) * WB;
     ContractLane c;
-    c.x = (float)(bx + (b & 7)) + 0.5f - 0.5f * TW;
-    c.y = (float)(by + (b >> 3)) + 3.5f - 0.5f * TH;      // mean of the four rows 2 t + b / 8
+    c.x = (float)(t.tx0 + bx + (b & 7)) + 0.5f;
+    c.y = (float)(t.ty0 + by + (b >> 3)) + 0.5f;
     c.slot = (lane & 12) == 0 ? 4 * row + (lane & 3) : -1;
     c.slot6 = (lane & 28) == 0 ? ((lane >> 5) == 0 ? (lane & 3) : ((lane & 2) == 0 ? 4 + (lane & 1) : -1)) : -1;
     return c;
@@ -818,19 +817,27 @@ __device__ __forceinline__ float4 wave_transpose4(float* scr, const float4& p) {
     return r;
 }
 
-// Sums over a wave of four values p, of each times y, of each times x (pixel
-// coordinates relative to the tile's middle), and of four values u, given
-// transposed as a and b: 16 sums, slots p 0..3, y p 4..7, x p 8..11, u 12..15
+// Sums over a wave of four values p, of each times dy, of each times dx (the
+// pixel relative to the projected centre cx, cy), and of four values u, given
+// transposed as a and b: 16 sums, slots p 0..3, dy p 4..7, dx p 8..11, u 12..15
 // of acc.  Every lane sums four pixels of one value after the transposition
-// in LDS, so the products with x and y are formed once per four pixels and
-// the cross-lane stages (permlane swaps, row rotations) carry four registers:
-// 19 VALU instructions, where 11 products and a transposed reduction of 15
-// registers took 46.
-__device__ __forceinline__ float wave_contract(const ContractLane& c, const float4& a, const float4& b) {
+// in LDS, so the product with dx is formed once per four pixels and the
+// cross-lane stages (permlane swaps, row rotations) carry four registers: 24
+// VALU instructions, where 11 products and a transposed reduction of 15
+// registers took 46.  The offsets are those from the splat's own centre: about
+// a point of the tile and shifted afterwards, the sums of a splat small
+// against its distance from that point cancel (19 instructions, but 16 times
+// the rounding at half a pixel).
+__device__ __forceinline__ float wave_contract(const ContractLane& c, float cx, float cy, const float4& a,
+                                               const float4& b) {
+#pragma clang fp contract(off)
     const float S = (a.x + a.w) + (a.y + a.z);
-    // rows 2 t + b / 8: the offsets from their mean are -3, -1, 1, 3
-    const float Y = __builtin_fmaf(c.y, S, __builtin_fmaf(3.0f, a.w - a.x, a.z - a.y));
-    const float X = c.x * S;
+    // rows 2 t + b / 8; the offsets of two rows differ by a whole number, so
+    // that every one is as exact as its own difference from the centre
+    const float dy = c.y - cy;
+    const float Y = __builtin_fmaf(a.x, dy, __builtin_fmaf(a.y, dy + 2.0f,
+                                   __builtin_fmaf(a.z, dy + 4.0f, a.w * (dy + 6.0f))));
+    const float X = (c.x - cx) * S;
     const float U = (b.x + b.w) + (b.y + b.z);
     const auto r0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(S), __float_as_uint(X), false, false);
     const auto r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(Y), __float_as_uint(U), false, false);
@@ -857,30 +864,27 @@ __device__ __forceinline__ float wave_sum6(const float4& a, float q) {
     return w;
 }
 
-// The component of a gradient record that flush lane l adds, from the sums
-// of an entry (the slots of wave_contract and, 16 on, of wave_sum6):
-// scale * (acc[at] + offset * acc[shift >> 1]), the offset the x (even shift)
-// or y (odd) of the tile's middle from the projected centre.
+// The component of a gradient record that flush lane l adds: scale * acc[at]
+// of the sums of an entry (the slots of wave_contract and, 16 on, of wave_sum6).
 struct GradTerm {
-    int comp, at, shift;      // comp < 0: none; shift < 0: no offset term
+    int comp, at;      // comp < 0: none
     float scale;
 };
 
 template <bool GEO>
 __device__ __forceinline__ GradTerm grad_term(int l) {
-    GradTerm t{-1, 0, -1, 1.0f};
+    GradTerm t{-1, 0, 1.0f};
     if (l < 9) {
-        const int i = l % 3, kind = l / 3;               // dA: x sums, dB: y sums, dC'
-        t = GradTerm{l, kind == 0 ? 8 + i : (kind == 1 ? 4 + i : i), kind == 2 ? -1 : 2 * i + kind,
-                     i == 2 ? -1.0f : 1.0f};             // the walk sums -dL/dw2
+        const int i = l % 3, kind = l / 3;               // dA: dx sums, dB: dy sums, dC'
+        t = GradTerm{l, kind == 0 ? 8 + i : (kind == 1 ? 4 + i : i), i == 2 ? -1.0f : 1.0f};   // the walk sums -dL/dw2
     } else if (l < 11) {
-        t = GradTerm{l, l == 9 ? 11 : 7, 2 * 3 + (l - 9), -2.0f};     // and -1/2 of the centre's
+        t = GradTerm{l, l == 9 ? 11 : 7, -2.0f};                      // and -1/2 of the centre's
     } else if (l == 11) {
-        t = GradTerm{11, 12, -1, 1.0f};
+        t = GradTerm{11, 12, 1.0f};
     } else if (!GEO) {
-        if (l < 15) t = GradTerm{l + 3, l + 1, -1, 1.0f};             // colour
+        if (l < 15) t = GradTerm{l + 3, l + 1, 1.0f};                 // colour
     } else if (l < 21) {
-        t = GradTerm{l, l < 15 ? l + 4 : (l < 18 ? l - 2 : l + 1), -1, 1.0f};     // m_z, colour, normal
+        t = GradTerm{l, l < 15 ? l + 4 : (l < 18 ? l - 2 : l + 1), 1.0f};     // m_z, colour, normal
     }
     return t;
 }
@@ -904,11 +908,10 @@ __device__ __forceinline__ GradTerm grad_term(int l) {
 //
 // VALU issue bounds this walk (one wave64 instruction per CU and cycle), and
 // the sums over the wave's 64 pixels were half of it.  They are a
-// contraction of a few per-pixel values with functions of the pixel that do
-// not depend on the entry: the columns A, B, C' of dL/dw and the low-pass
-// centre are the sums of {dw0, dw1, dw2, f2} times {x, y, 1}, so only those
-// four values and four plain sums (opacity, colour) go through the
-// reduction, not 15 products.
+// contraction: the columns A, B, C' of dL/dw and the low-pass centre are the
+// sums of {dw0, dw1, dw2, f2} times {dx, dy, 1}, and dx and dy depend on the
+// pixel's column and row alone, so only those four values and four plain sums
+// (opacity, colour) go through the reduction, not 15 products.
 template <int TW, int NT, int BATCH, bool GEO, bool SCALAR, bool HITS>
 __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, int N, const float4* __restrict__ geom,
                                          const float4* __restrict__ app, const uint32_t* __restrict__ vals,
@@ -951,7 +954,7 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
     const float4* geom_v = geom + kGeomF4 * (size_t)t.v * N;
     const float4* app_v = app + kAppF4 * (size_t)t.v * N;
     float* scr = reinterpret_cast<float*>(&sm.xp[64 * wv]);
-    const ContractLane cr = contract_lane<TW, TH>();
+    const ContractLane cr = contract_lane<TW>(t);
     static_assert(NT / 64 <= kMaxWaves, "gathering counts");
     // batches of up to BATCH entries of the tile below run position hi,
     // gathered from its group's run highest first into slots [lo, BATCH)
@@ -973,7 +976,6 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
 #pragma unroll
                 for (int q = 0; q < kGeomF4; ++q) gq[q] = geom_v[kGeomF4 * (size_t)g + q];
                 sm.rec.put(tid, gq, app_v + kAppF4 * (size_t)g);
-                sm.mid[tid] = make_float2((float)(t.tx0 + TW / 2) - gq[2].y, (float)(t.ty0 + TH / 2) - gq[2].z);
                 // the forward's wave bits of this position when cached
                 const uint32_t bits = (bitcache && jpos < BitCache<NT>::kPos)
                                           ? (bitcache[jpos >> 3] >> ((jpos & 7u) << 2)) & 0xFu
@@ -1079,7 +1081,7 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
                 wave_lds_order();
                 w6 = wave_sum6(tc, q);
             }
-            float w16 = wave_contract(cr, ta, tb);
+            float w16 = wave_contract(cr, sg.cx, sg.cy, ta, tb);
             // summed before the branches: sunk below them, the last adds need moves of their own
             asm volatile("" : "+v"(w16), "+v"(w6));
             if (cr.slot >= 0) atomicAdd(&sm.acc[k][cr.slot], w16);
@@ -1115,13 +1117,9 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
             const int e = list[n];
             const uint32_t g = sm.id[e] & kInstIdMask;
             const size_t r = (size_t)t.v * N + g;
-            // the sums refer to the tile's middle: dx = (px - middle) + (middle - cx)
-            const float* A = sm.acc[e];
             float v = 0.f;
             if (term.comp >= 0) {
-                v = A[term.at];
-                if (term.shift >= 0) v = __builtin_fmaf(term.shift & 1 ? sm.mid[e].y : sm.mid[e].x, A[term.shift >> 1], v);
-                v *= term.scale;
+                v = sm.acc[e][term.at] * term.scale;
                 if (v != 0.f) atomicAdd(&grad_rec[r * SR_GRAD_STRIDE + term.comp], v);
             }
             // mark the record for the projection backward (bit 31)

@@ -309,9 +309,10 @@ k_ssim_bwd(const sr_camera* __restrict__ cams, int V, const float* __restrict__ 
     }
 }
 
-// out[v] = SSIM_v, out[V+v] = PSNR_v (one block per view)
+// out[v] = SSIM_v, out[V+v] = PSNR_v (one block per view); the total of a
+// single view, written with its terms (one launch less)
 __global__ void __launch_bounds__(kNT)
-k_ssim_final(const sr_camera* __restrict__ cams, int V, int nslot, const float* __restrict__ partial,
+k_ssim_final(const sr_camera* __restrict__ cams, int V, int nslot, const float* __restrict__ partial, float w_s,
              float* __restrict__ out) {
     __shared__ float2 s[kNT / 64];
     const int v = blockIdx.x;
@@ -324,8 +325,10 @@ k_ssim_final(const sr_camera* __restrict__ cams, int V, int nslot, const float* 
     const float2 sum = block_sum2(a, b, s);
     if (threadIdx.x == 0) {
         const float n = 3.0f * (float)cams[v].width * (float)cams[v].height;
-        out[v] = sum.x / n;
+        const float ssim = sum.x / n;
+        out[v] = ssim;
         out[V + v] = -10.0f * log10f(sum.y / n);
+        if (V == 1) out[2] = w_s * (1.0f - ssim);
     }
 }
 
@@ -377,8 +380,8 @@ hipError_t launch_ssim(int V, int max_slots, int total_slots, int64_t P, const s
     if (dL_dcolor)
         hipLaunchKernelGGL(k_ssim_bwd, dim3(total_slots), dim3(kNT), 0, s, cams, V, color, target, mask, taps, P3,
                            (const float*)gmaps, dL_dcolor);
-    hipLaunchKernelGGL(k_ssim_final, dim3(V), dim3(kNT), 0, s, cams, V, max_slots, (const float*)partial, out);
-    hipLaunchKernelGGL(k_ssim_total, dim3(1), dim3(kNT), 0, s, V, w_s, out);
+    hipLaunchKernelGGL(k_ssim_final, dim3(V), dim3(kNT), 0, s, cams, V, max_slots, (const float*)partial, w_s, out);
+    if (V > 1) hipLaunchKernelGGL(k_ssim_total, dim3(1), dim3(kNT), 0, s, V, w_s, out);
     return hipGetLastError();
 }
 

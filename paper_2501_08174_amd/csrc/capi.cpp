@@ -24,6 +24,7 @@ struct sr_ctx {
     int device;
     uint32_t* status;
     float* scratch;     // the device's scratch array (sr_train_step_raster_noalloc)
+    int simds;          // SIMDs of the device (four per compute unit)
 };
 
 namespace {
@@ -145,12 +146,14 @@ sr_status sr_create(sr_ctx** ctx_out_host, int32_t device) {
     if (e == hipSuccess) e = hipDeviceSynchronize();
     // the address of this device's copy of the scratch array, with the device current
     if (e == hipSuccess) e = sr::scratch_address(device, &scratch);
+    int cus = 0;
+    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device);
     hipSetDevice(prev);
     if (e != hipSuccess) {
         if (p) hipFree(p);
         return hip_status(e, "sr_create");
     }
-    sr_ctx* c = new (std::nothrow) sr_ctx{device, (uint32_t*)p, scratch};
+    sr_ctx* c = new (std::nothrow) sr_ctx{device, (uint32_t*)p, scratch, 4 * cus};
     if (!c) {
         hipFree(p);
         return fail(SR_ERR_ARG, "out of host memory");
@@ -327,7 +330,7 @@ sr_status sr_render_forward(sr_ctx* ctx, const sr_config* cfg, int32_t N, int32_
     return hip_status(sr::launch_render_fwd(*cfg, N, V, total_tiles, cams_dev, geom, app, nullptr, vals, ranges,
                                             color, alpha, depth, normal, dist, T_final, n_contrib, hits, max_alpha,
                                             max_weight, nullptr, median_depth, median_contrib, tile_order,
-                                            tile_cost, ctx->status, s),
+                                            tile_cost, ctx->status, ctx->simds, s),
                       "sr_render_forward");
 }
 
@@ -381,7 +384,7 @@ sr_status sr_backward_raster(sr_ctx* ctx, const sr_config* cfg, int32_t N, int32
     return hip_status(sr::launch_render_bwd(*cfg, N, V, total_tiles, cams_dev, geom, app, vals, ranges, alpha, depth,
                                             dist, T_final, n_contrib, dL_dcolor, dL_dalpha, dL_ddepth, dL_dnormal,
                                             dL_ddist, median_contrib, dL_dmedian, grad_rec, grad_marks, tile_order,
-                                            ctx->status, (hipStream_t)stream),
+                                            ctx->status, ctx->simds, (hipStream_t)stream),
                       "sr_backward_raster");
 }
 
@@ -427,7 +430,7 @@ sr_status sr_render_backward(sr_ctx* ctx, const sr_config* cfg, int32_t N, int32
     SR_TRY(hip_status(sr::launch_render_bwd(*cfg, N, V, total_tiles, cams_dev, geom, app, vals, ranges, alpha, depth,
                                             dist, T_final, n_contrib, dL_dcolor, dL_dalpha, dL_ddepth, dL_dnormal,
                                             dL_ddist, median_contrib, dL_dmedian, grad_rec, nullptr, nullptr,
-                                            ctx->status, s),
+                                            ctx->status, ctx->simds, s),
                       "render backward"));
     sr_config pcfg = *cfg;
     pcfg.flags &= ~SR_FLAG_MARKED_GRADIENTS;     // no marks here: every record is read
@@ -652,7 +655,7 @@ sr_status sr_prune_stats(sr_ctx* ctx, const sr_config* cfg, int32_t N, int32_t V
     return hip_status(sr::launch_render_fwd(*cfg, N, V, total_tiles, cams_dev, geom, nullptr, rect, vals, ranges,
                                             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, hits,
                                             max_alpha, max_weight, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                            ctx->status, s),
+                                            ctx->status, ctx->simds, s),
                       "sr_prune_stats");
 }
 
@@ -693,7 +696,7 @@ sr_status train_step(sr_ctx* ctx, const sr_config* cfg, int32_t N, int32_t V, co
     SR_TRY(hip_status(sr::launch_train_raster(*cfg, N, V, total_tiles, cams_dev, geom, app, vals, ranges, mask, target,
                                               gamma, w_c, color, alpha, depth, normal, dist, T_final, n_contrib, hits,
                                               max_alpha, max_weight, tile_loss, grad_rec, grad_marks, tile_order,
-                                              tile_cost, ctx->status, s),
+                                              tile_cost, ctx->status, ctx->simds, s),
                       "sr_train_step_raster"));
     return hip_status(sr::launch_loss_from_tiles(V, cams_dev, tile_loss, gamma, w_c, loss, s), "loss totals");
 }
@@ -741,7 +744,7 @@ sr_status sr_render_count(sr_ctx* ctx, const sr_config* cfg, int32_t N, int32_t 
                                             nullptr,
                                             nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                                             nullptr, (unsigned long long*)counts, nullptr, nullptr, nullptr, nullptr,
-                                            ctx->status, s),
+                                            ctx->status, ctx->simds, s),
                       "sr_render_count");
 }
 
@@ -989,7 +992,7 @@ sr_status sr_prune_contrib(sr_ctx* ctx, const sr_config* cfg, int32_t prim, int3
                                                     (const uint16_t*)(ws + L.rect), vals, ranges, nullptr, nullptr,
                                                     nullptr, nullptr, nullptr, nullptr, nullptr, hits, max_alpha,
                                                     max_weight, nullptr, nullptr, nullptr, nullptr, nullptr,
-                                                    ctx->status, s),
+                                                    ctx->status, ctx->simds, s),
                               "prune pass: statistics"));
         else
             SR_TRY(hip_status(sr::launch_prune3d(c, N, v1 - v0, tiles, dc, (const float*)(ws + L.geom), vals, ranges,

@@ -40,13 +40,14 @@ bool bwd_batch_supported(int tw, int th, int batch);
 
 hipError_t fill_f32(float* p, float v, uint64_t n, hipStream_t s);
 
+// simds: SIMDs of the device
 hipError_t launch_render_fwd(const sr_config& cfg, int N, int V, int total_tiles, const sr_camera* cams,
                              const float* geom, const float* app, const uint16_t* rect, const uint32_t* vals,
                              const uint32_t* ranges, float* color, float* alpha, float* depth, float* normal,
                              float* dist, float* T_final,
                              uint32_t* n_contrib, uint32_t* hits, float* max_alpha, float* max_weight,
                              unsigned long long* counts, float* median_depth, uint32_t* median_contrib,
-                             const uint32_t* tile_order, uint32_t* tile_cost, const uint32_t* status,
+                             const uint32_t* tile_order, uint32_t* tile_cost, const uint32_t* status, int simds,
                              hipStream_t s);
 
 hipError_t launch_render_bwd(const sr_config& cfg, int N, int V, int total_tiles, const sr_camera* cams,
@@ -55,7 +56,7 @@ hipError_t launch_render_bwd(const sr_config& cfg, int N, int V, int total_tiles
                              const uint32_t* n_contrib, const float* dC, const float* dA, const float* dD,
                              const float* dN, const float* dS, const uint32_t* median_contrib, const float* dMed,
                              float* grad_rec, uint32_t* grad_marks, const uint32_t* tile_order,
-                             const uint32_t* status, hipStream_t s);
+                             const uint32_t* status, int simds, hipStream_t s);
 
 hipError_t launch_train_raster(const sr_config& cfg, int N, int V, int total_tiles, const sr_camera* cams,
                                const float* geom, const float* app, const uint32_t* vals, const uint32_t* ranges,
@@ -63,7 +64,7 @@ hipError_t launch_train_raster(const sr_config& cfg, int N, int V, int total_til
                                float* alpha, float* depth, float* normal, float* dist, float* T_final,
                                uint32_t* n_contrib, uint32_t* hits, float* max_alpha, float* max_weight,
                                float* tile_loss, float* grad_rec, uint32_t* grad_marks, const uint32_t* tile_order,
-                               uint32_t* tile_cost, const uint32_t* status, hipStream_t s);
+                               uint32_t* tile_cost, const uint32_t* status, int simds, hipStream_t s);
 
 // The device address of the training step's file-scope scratch array on
 // `device` (which must be current at the first call for that device).

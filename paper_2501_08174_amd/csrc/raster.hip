@@ -102,12 +102,12 @@ constexpr int kMaxWaves = 8;    // waves per workgroup (tiles of up to 512 pixel
 // per staged entry.  Measured with scalar records (compositing kernel; 1M
 // surfels x 16 views / 3M x 8 / one 800x800 view of 100k): training step 6.64 /
 // 5.47 / 0.372 ms at five, 6.13 / 5.13 / 0.369 at six, 5.93 / 4.97 / 0.381 at
-// seven; forward of four 1559x1039 views 1.07 / 1.00 / 1.02 ms at five to
-// seven; backward with the depth terms 2.33 / 2.29 ms there but 0.42 / 0.45 on
-// one 800x600 view; the pruning pass of 100 views 50.5 / 50.5 / 49.7 ms.  With
-// records in LDS (few tiles) four and five measure the same.
+// seven; backward with the depth terms of four 1559x1039 views 2.33 / 2.29 ms
+// but 0.42 / 0.45 on one 800x600 view; the pruning pass of 100 views 50.5 /
+// 50.5 / 49.7 ms.  With records in LDS (the forward, and where tiles are few)
+// four and five measure the same.
 #define SR_OCCUPANCY(waves) __attribute__((amdgpu_waves_per_eu(waves)))
-constexpr int kFwdWaves = 6, kPruneWaves = 7, kBwdWaves = 5, kTrainWaves = 6, kLdsWaves = 5, kAheadWaves = 4;
+constexpr int kPruneWaves = 7, kBwdWaves = 5, kTrainWaves = 6, kLdsWaves = 5, kAheadWaves = 4;
 
 // MODE bits: 1 shade (colour, depth, normal, distortion outputs), 2 occlusion
 // statistics, 4 count reached/blended pairs (work accounting), 8 median depth
@@ -230,11 +230,12 @@ __device__ __forceinline__ uint32_t wave_bits(const float4& g0, const float4& g1
 //   the kernel's time.  A vector instruction takes one scalar operand, so the
 //   addends C, which meet a second one, come from LDS (staged in c, with
 //   twice the cutoff in the fourth slot).
-// else: broadcasts from LDS.  Where few tiles leave every SIMD a wave or two,
-//   nothing hides a scalar load that misses its cache, and a wave's own
-//   latency per entry is the kernel's time; the LDS unit is then idle.
+// else: broadcasts from LDS.  Where the launch holds few waves, nothing hides
+//   a scalar load that misses its cache, and a wave's own latency per entry is
+//   the kernel's time; the LDS unit is then idle.  The forward with outputs
+//   measures faster so at every size.
 //
-// The rule is on the number of tiles (scalar_records).
+// The rule is on the waves of the launch (scalar_records).
 typedef float F16v __attribute__((ext_vector_type(16)));
 typedef float F4v __attribute__((ext_vector_type(4)));
 typedef float F2v __attribute__((ext_vector_type(2)));
@@ -698,7 +699,7 @@ __device__ __forceinline__ void write_outputs(const PixFwd& st, const PixOut& o,
 }
 
 template <int TW, int TH, int MODE, bool SCALAR>
-__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(!SCALAR ? kLdsWaves : (MODE & kShade) ? kFwdWaves : kPruneWaves)
+__global__ void __launch_bounds__(TW * TH) SR_OCCUPANCY(SCALAR ? kPruneWaves : kLdsWaves)
 k_render_fwd(const sr_camera* __restrict__ cams, int V, int N, const float4* __restrict__ geom,
              const float4* __restrict__ app, const uint2* __restrict__ rect, const uint32_t* __restrict__ vals,
              const uint2* __restrict__ ranges,
@@ -1303,16 +1304,23 @@ bool with_batch(int batch, F&& f) {
 }
 
 // Where the entries' records are read from (EntryRec): through the scalar
-// cache from this many pixels of tiles on, from LDS below.  With fewer tiles a
-// SIMD holds one or two waves and the scalar loads' latency shows; with more,
-// the other waves cover it and the LDS reads would fill the LDS unit.
-// Measured (scalar / LDS): training step of 16.6 Mpx 8.27 / 9.39 ms, of one
-// 800x800 view 0.703 / 0.706, of three small views 3.72 / 3.35; backward with
-// the depth terms in iterations of 800x600 1.136 / 1.148 and of two 441x280
-// views 3.87 / 3.68; forwards of 6.5 Mpx (in a 4-view Eq. 3 pass) 4.99 / 5.40,
-// of one 1237x822 view 0.692 / 0.684, of one 131x145 view 4.29 / 3.86.
-constexpr int64_t kScalarFwdPixels = 2000000, kScalarBwdPixels = 450000;
-inline bool scalar_records(int64_t pixels, int64_t from) { return pixels >= from; }
+// cache from so many waves per SIMD of the device on (all waves of the launch
+// over all SIMDs), from LDS below.  A SIMD holds five to seven at a time; with
+// few rounds of them the launch ends with the chains of its longest tiles,
+// each wave alone with the latency of its loads, with many the other waves
+// cover it and the LDS reads would fill the LDS unit.  The limits are the
+// crossovers of a sweep (5 thousand to 1.5 million surfels, 1 to 16 views, 0.06
+// to 256 waves per SIMD, the four tile shapes; LDS / scalar time, geometric
+// means by waves per SIMD):
+//   backward with depth terms  0.99 at 5, 1.00 at 6, 1.01 at 8, 1.07 at 14, 1.20 at 100
+//   backward, colour and alpha 0.95 at 6, 0.98 at 12, 1.03 at 14, 1.10 at 18, 1.18 at 100
+//   training step              0.96 at 12, 0.98 at 14, 0.97 at 16, 1.08 at 18, 1.19 at 100
+//   pruning statistics         0.95 at 12, 0.98 at 23, 1.00 at 28, 1.03 at 100, 1.05 at 250
+//   forward with outputs       0.98 at 6, 0.96 at 12, 0.97 at 28 and at 100: from LDS always
+constexpr int kScalarGeoWaves = 8, kScalarBwdWaves = 14, kScalarTrainWaves = 16, kScalarPruneWaves = 28;
+inline bool scalar_records(int tiles, int tile_pixels, int simds, int waves) {
+    return (int64_t)tiles * (tile_pixels / 64) >= (int64_t)waves * simds;
+}
 
 template <int TW, int TH, int MODE>
 void fwd_launch(int total_tiles, hipStream_t s, const sr_camera* cams, int V, int N, const float4* geom,
@@ -1320,9 +1328,12 @@ void fwd_launch(int total_tiles, hipStream_t s, const sr_camera* cams, int V, in
                 float* color,
                 float* alpha, float* depth, float* normal, float* dist, float* T_final, uint32_t* n_contrib,
                 uint32_t* hits, float* max_alpha, float* max_weight, unsigned long long* counts,
-                float* median_depth, uint32_t* median_contrib, const uint32_t* tile_order, uint32_t* tile_cost) {
-    auto k = scalar_records((int64_t)total_tiles * TW * TH, kScalarFwdPixels) ? k_render_fwd<TW, TH, MODE, true>
-                                                                      : k_render_fwd<TW, TH, MODE, false>;
+                float* median_depth, uint32_t* median_contrib, const uint32_t* tile_order, uint32_t* tile_cost,
+                int simds) {
+    auto k = k_render_fwd<TW, TH, MODE, false>;
+    if constexpr ((MODE & kStats) != 0 && (MODE & kShade) == 0) {
+        if (scalar_records(total_tiles, TW * TH, simds, kScalarPruneWaves)) k = k_render_fwd<TW, TH, MODE, true>;
+    }
     hipLaunchKernelGGL(k, dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app,
                        rect, vals, ranges, rc, color, alpha, depth, normal, dist, T_final, n_contrib, hits, max_alpha,
                        max_weight, counts, median_depth, median_contrib, tile_order, tile_cost);
@@ -1334,11 +1345,11 @@ bool fwd_dispatch(int mode, int total_tiles, hipStream_t s, const sr_camera* cam
                   RasterConsts rc, float* color, float* alpha, float* depth, float* normal, float* dist,
                   float* T_final, uint32_t* n_contrib, uint32_t* hits, float* max_alpha, float* max_weight,
                   unsigned long long* counts, float* median_depth, uint32_t* median_contrib,
-                  const uint32_t* tile_order, uint32_t* tile_cost) {
+                  const uint32_t* tile_order, uint32_t* tile_cost, int simds) {
 #define SR_FWD(M)                                                                                        \
     fwd_launch<TW, TH, M>(total_tiles, s, cams, V, N, geom, app, rect, vals, ranges, rc, color, alpha, depth, \
                           normal, dist, T_final, n_contrib, hits, max_alpha, max_weight, counts,          \
-                          median_depth, median_contrib, tile_order, tile_cost)
+                          median_depth, median_contrib, tile_order, tile_cost, simds)
     switch (mode) {
         case kShade: SR_FWD(kShade); return true;
         case kShade | kHits: SR_FWD(kShade | kHits); return true;
@@ -1360,11 +1371,11 @@ bool bwd_launch(int batch, int total_tiles, hipStream_t s, const sr_camera* cams
                 const float* depth, const float* dist, const float* T_final, const uint32_t* n_contrib,
                 const float* dC, const float* dA, const float* dD, const float* dN, const float* dS,
                 const uint32_t* median_contrib, const float* dMed, float* grad_rec, uint32_t* grad_marks,
-                const uint32_t* tile_order) {
+                const uint32_t* tile_order, int simds) {
     const bool geo = dD || dN || dS || dMed;
     return with_batch<TW * TH>(resolve_batch(TW * TH, batch), [&](auto bc) {
         constexpr int B = decltype(bc)::value;
-        const bool sc = scalar_records((int64_t)total_tiles * TW * TH, kScalarBwdPixels);
+        const bool sc = scalar_records(total_tiles, TW * TH, simds, geo ? kScalarGeoWaves : kScalarBwdWaves);
         auto k = geo ? (sc ? k_render_bwd<TW, TH, B, true, true> : k_render_bwd<TW, TH, B, true, false>)
                      : (sc ? k_render_bwd<TW, TH, B, false, true> : k_render_bwd<TW, TH, B, false, false>);
         hipLaunchKernelGGL(k, dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app, vals, ranges, rc, alpha,
@@ -1380,10 +1391,10 @@ bool train_launch(int stats, int batch, int total_tiles, hipStream_t s, const sr
                   float* depth, float* normal, float* dist, float* T_final, uint32_t* n_contrib, uint32_t* hits,
                   float* max_alpha, float* max_weight, float* tile_loss, float* grad_rec, uint32_t* grad_marks,
                   const uint32_t* tile_order,
-                  uint32_t* tile_cost) {
+                  uint32_t* tile_cost, int simds) {
     return with_batch<TW * TH>(resolve_batch(TW * TH, batch), [&](auto bc) {
         constexpr int B = decltype(bc)::value;
-        const bool sc = scalar_records((int64_t)total_tiles * TW * TH, kScalarBwdPixels);
+        const bool sc = scalar_records(total_tiles, TW * TH, simds, kScalarTrainWaves);
 #define SR_TRAIN(S)                                                                                              \
     hipLaunchKernelGGL((sc ? k_train_raster<TW, TH, B, S, true> : k_train_raster<TW, TH, B, S, false>),         \
                        dim3(total_tiles), dim3(TW * TH), 0, s, cams, V, N, geom, app, vals, ranges, rc, mask,    \
@@ -1430,7 +1441,7 @@ hipError_t launch_render_fwd(const sr_config& cfg, int N, int V, int total_tiles
                              float* dist, float* T_final, uint32_t* n_contrib, uint32_t* hits, float* max_alpha,
                              float* max_weight, unsigned long long* counts, float* median_depth,
                              uint32_t* median_contrib, const uint32_t* tile_order, uint32_t* tile_cost,
-                             const uint32_t* status, hipStream_t s) {
+                             const uint32_t* status, int simds, hipStream_t s) {
     if (total_tiles == 0) return hipSuccess;
     RasterConsts rc{cfg.alpha_min, cfg.alpha_max, cfg.t_min, cfg.flags, status};
     const int stats = hits ? (max_alpha ? kStats : kHits) : 0;
@@ -1442,7 +1453,7 @@ hipError_t launch_render_fwd(const sr_config& cfg, int N, int V, int total_tiles
         if (!fwd_dispatch<W, H>(mode, total_tiles, s, cams, V, N, (const float4*)geom, (const float4*)app,     \
                                 (const uint2*)rect, vals, (const uint2*)ranges, rc, color, alpha, depth, normal, \
                                 dist, T_final, n_contrib, hits, max_alpha, max_weight, counts, median_depth,     \
-                                median_contrib, tile_order, tile_cost))                                         \
+                                median_contrib, tile_order, tile_cost, simds))                                     \
             return hipErrorInvalidValue;                                                                        \
         return hipGetLastError();                                                                               \
     }
@@ -1457,7 +1468,7 @@ hipError_t launch_render_bwd(const sr_config& cfg, int N, int V, int total_tiles
                              const uint32_t* n_contrib, const float* dC, const float* dA, const float* dD,
                              const float* dN, const float* dS, const uint32_t* median_contrib, const float* dMed,
                              float* grad_rec, uint32_t* grad_marks, const uint32_t* tile_order,
-                             const uint32_t* status, hipStream_t s) {
+                             const uint32_t* status, int simds, hipStream_t s) {
     if (total_tiles == 0) return hipSuccess;
     RasterConsts rc{cfg.alpha_min, cfg.alpha_max, cfg.t_min, cfg.flags, status};
 #define SR_TS(W, H)                                                                                            \
@@ -1465,7 +1476,7 @@ hipError_t launch_render_bwd(const sr_config& cfg, int N, int V, int total_tiles
         if (!bwd_launch<W, H>(cfg.bwd_batch, total_tiles, s, cams, V, N, (const float4*)geom,                 \
                               (const float4*)app, vals, (const uint2*)ranges, rc, alpha, depth, dist, T_final,  \
                               n_contrib, dC, dA, dD, dN, dS, median_contrib, dMed, grad_rec, grad_marks,       \
-                              tile_order))                                                                      \
+                              tile_order, simds))                                                               \
             return hipErrorInvalidValue;                                                                      \
         return hipGetLastError();                                                                             \
     }
@@ -1481,7 +1492,7 @@ hipError_t launch_train_raster(const sr_config& cfg, int N, int V, int total_til
                                uint32_t* n_contrib, uint32_t* hits, float* max_alpha, float* max_weight,
                                float* tile_loss, float* grad_rec, uint32_t* grad_marks, const uint32_t* tile_order,
                                uint32_t* tile_cost,
-                               const uint32_t* status, hipStream_t s) {
+                               const uint32_t* status, int simds, hipStream_t s) {
     if (total_tiles == 0) return hipSuccess;
     RasterConsts rc{cfg.alpha_min, cfg.alpha_max, cfg.t_min, cfg.flags, status};
 #define SR_TS(W, H)                                                                                               \
@@ -1489,7 +1500,8 @@ hipError_t launch_train_raster(const sr_config& cfg, int N, int V, int total_til
         if (!train_launch<W, H>(hits ? (max_alpha ? 2 : 1) : 0, cfg.bwd_batch, total_tiles, s, cams, V, N,      \
                                 (const float4*)geom, (const float4*)app, vals, (const uint2*)ranges, rc, mask,   \
                                 target, gamma, w_c, color, alpha, depth, normal, dist, T_final, n_contrib, hits, \
-                                max_alpha, max_weight, tile_loss, grad_rec, grad_marks, tile_order, tile_cost)) \
+                                max_alpha, max_weight, tile_loss, grad_rec, grad_marks, tile_order, tile_cost,  \
+                                simds))                                                                          \
             return hipErrorInvalidValue;                                                                         \
         return hipGetLastError();                                                                                \
     }

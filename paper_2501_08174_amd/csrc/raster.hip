@@ -533,8 +533,6 @@ __device__ __forceinline__ void fwd_tile(const TileCtx& t, float px, float py, i
           if constexpr (SCALAR) {
             load_scalar<SHADE, SHADE>(geom_v, app_v, __builtin_amdgcn_readlane(my_id, nbit) & kInstIdMask, next_rec);
             next_rec.c = sm.rec.c[c * 64 + nbit];
-          } else {
-            load_lds_test(sm.rec, c * 64 + nbit, next_rec);
           }
           // HITS: this wave's blended pixels of entry c * 64 + lane
           uint32_t my_hits = 0;

@@ -817,7 +817,7 @@ __device__ __forceinline__ float4 wave_transpose4(float* scr, const float4& p) {
 }
 
 // Sums over a wave of four values p, of each times dy, of each times dx (the
-// pixel relative to the projected centre cx, cy), and of four values u, given
+// pixel relative to the projected centre), and of four values u, given
 // transposed as a and b: 16 sums, slots p 0..3, dy p 4..7, dx p 8..11, u 12..15
 // of acc.  Every lane sums four pixels of one value after the transposition
 // in LDS, so the product with dx is formed once per four pixels and the
@@ -827,16 +827,16 @@ __device__ __forceinline__ float4 wave_transpose4(float* scr, const float4& p) {
 // a point of the tile and shifted afterwards, the sums of a splat small
 // against its distance from that point cancel (19 instructions, but 16 times
 // the rounding at half a pixel).
-__device__ __forceinline__ float wave_contract(const ContractLane& c, float cx, float cy, const float4& a,
+__device__ __forceinline__ float wave_contract(const ContractLane& c, float2 centre, const float4& a,
                                                const float4& b) {
 #pragma clang fp contract(off)
     const float S = (a.x + a.w) + (a.y + a.z);
     // rows 2 t + b / 8; the offsets of two rows differ by a whole number, so
     // that every one is as exact as its own difference from the centre
-    const float dy = c.y - cy;
+    const float dy = c.y - centre.y;
     const float Y = __builtin_fmaf(a.x, dy, __builtin_fmaf(a.y, dy + 2.0f,
                                    __builtin_fmaf(a.z, dy + 4.0f, a.w * (dy + 6.0f))));
-    const float X = (c.x - cx) * S;
+    const float X = (c.x - centre.x) * S;
     const float U = (b.x + b.w) + (b.y + b.z);
     const auto r0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(S), __float_as_uint(X), false, false);
     const auto r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(Y), __float_as_uint(U), false, false);
@@ -1021,6 +1021,17 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
                 if constexpr (!AHEAD) load_lds_test(sm.rec, k, rec);
                 load_lds_rest<true>(sm.rec, k, rec);
             }
+            // AHEAD: the centre is read again with the opacity, so that the next
+            // entry's test takes the registers of this one's (kept for the sums
+            // it cost nine moves an entry)
+            float2 centre;
+            if constexpr (AHEAD) {
+                const float4 g2 = sm.rec.g[2][k];
+                rec.g[11] = g2.w;
+                centre = make_float2(g2.y, g2.z);
+            } else {
+                centre = make_float2(rec.g[9], rec.g[10]);
+            }
             const SurfelGeom sg = geom_of<SCALAR>(rec);
             PairEval e;
             eval_test<SCALAR>(sg, px, py, e);
@@ -1071,16 +1082,20 @@ __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, i
             const float f2 = e.surf ? 0.f : dLdrho;           // -1/2 of the centre's
             const float4 ta = wave_transpose4(scr, make_float4(dw0, dw1, dw2, f2));
             const float4 tb = wave_transpose4(scr, make_float4(dLdo, pb.gC0 * wgt, pb.gC1 * wgt, pb.gC2 * wgt));
-            float w6 = 0.f;
+            float4 tc;
+            float q0 = 0.f, q1 = 0.f;
             if (GEO) {
-                const float4 tc = wave_transpose4(scr, make_float4(dzs * us, dzs * vs, dLdz, pb.gN0 * wgt));
+                tc = wave_transpose4(scr, make_float4(dzs * us, dzs * vs, dLdz, pb.gN0 * wgt));
                 reinterpret_cast<float2*>(scr)[lane] = make_float2(pb.gN1 * wgt, pb.gN2 * wgt);
                 wave_lds_order();
-                const float q = scr[lane] + scr[64 + lane];      // value lane & 1 of two pixels
+                q0 = scr[lane];                                  // value lane & 1 of two pixels
+                q1 = scr[64 + lane];
                 wave_lds_order();
-                w6 = wave_sum6(tc, q);
             }
-            float w16 = wave_contract(cr, sg.cx, sg.cy, ta, tb);
+            float w16 = wave_contract(cr, centre, ta, tb);
+            // a lone wave: not before the contraction, whose values were read first
+            if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
+            float w6 = GEO ? wave_sum6(tc, q0 + q1) : 0.f;
             // summed before the branches: sunk below them, the last adds need moves of their own
             asm volatile("" : "+v"(w16), "+v"(w6));
             if (cr.slot >= 0) atomicAdd(&sm.acc[k][cr.slot], w16);

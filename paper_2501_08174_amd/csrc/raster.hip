@@ -1325,12 +1325,12 @@ bool with_batch(int batch, F&& f) {
 // crossovers of a sweep (5 thousand to 1.5 million surfels, 1 to 16 views, 0.06
 // to 256 waves per SIMD, the four tile shapes; LDS / scalar time, geometric
 // means by waves per SIMD):
-//   backward with depth terms  0.99 at 5, 1.00 at 6, 1.01 at 8, 1.07 at 14, 1.20 at 100
-//   backward, colour and alpha 0.95 at 6, 0.98 at 12, 1.03 at 14, 1.10 at 18, 1.18 at 100
-//   training step              0.96 at 12, 0.98 at 14, 0.97 at 16, 1.08 at 18, 1.19 at 100
-//   pruning statistics         0.95 at 12, 0.98 at 23, 1.00 at 28, 1.03 at 100, 1.05 at 250
+//   backward with depth terms  0.98 at 5, 1.00 at 8, 1.01 at 10, 1.06 at 13, 1.21 at 100
+//   backward, colour and alpha 0.96 at 6, 0.98 at 10, 1.02 at 13, 1.04 at 16, 1.18 at 100
+//   training step              0.96 at 10, 0.98 at 13, 0.99 at 16, 1.04 at 20, 1.17 at 100
+//   pruning statistics         0.93 at 10, 0.97 at 20, 0.99 at 25, 1.01 at 32, 1.05 at 250
 //   forward with outputs       0.98 at 6, 0.96 at 12, 0.97 at 28 and at 100: from LDS always
-constexpr int kScalarGeoWaves = 8, kScalarBwdWaves = 14, kScalarTrainWaves = 16, kScalarPruneWaves = 28;
+constexpr int kScalarGeoWaves = 10, kScalarBwdWaves = 14, kScalarTrainWaves = 18, kScalarPruneWaves = 28;
 inline bool scalar_records(int tiles, int tile_pixels, int simds, int waves) {
     return (int64_t)tiles * (tile_pixels / 64) >= (int64_t)waves * simds;
 }

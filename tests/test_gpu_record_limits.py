@@ -9,7 +9,7 @@ from tests.test_gpu_records import SMALL, _camera, _params, _run
 
 pytestmark = pytest.mark.gpu
 
-LIMITS = {"eq3": 8, "colour": 14, "train": 16, "prune": 28}
+LIMITS = {"eq3": 10, "colour": 14, "train": 18, "prune": 28}
 
 
 def _away(tiles, tile):

@@ -39,7 +39,7 @@ sys.path.insert(0, ROOT)
 # ~26 per skipped pair.
 FWD_OPS_BLEND, FWD_OPS_SKIP = 45.0, 26.0
 BWD_OPS_BLEND, BWD_OPS_SKIP = 110.0, 26.0
-VALU_PEAK = 256 * 64 * 2.4e9          # lane-ops/s: 256 CUs x 64 lanes x 2.4 GHz
+VALU_PEAK = 256 * 128 * 2.4e9         # lane-ops/s: 256 CUs x 128 FP32 lanes x 2.4 GHz (157.3 TFLOP/s of FMAs)
 HBM_PEAK = 8.0e12                      # bytes/s
 # masked D-SSIM with its gradient, per pixel: colour and target read (24 B),
 # mask (1 B), the colour gradient read and written (24 B); per channel 5

@@ -227,7 +227,8 @@ __device__ __forceinline__ uint32_t wave_bits(const float4& g0, const float4& g1
 // SCALAR: through the scalar cache into scalar registers, 18 to 24 words in
 //   two or three loads, fetched one entry ahead.  Read as broadcasts from LDS
 //   (six 16-byte reads) the records kept the LDS unit busy for two thirds of
-//   the kernel's time.  A vector instruction takes one scalar operand, so the
+//   the kernel's time.  (The price: an instruction with a scalar operand issues
+//   at little over half the rate.)  A vector instruction takes one, so the
 //   addends C, which meet a second one, come from LDS (staged in c, with
 //   twice the cutoff in the fourth slot).
 // else: broadcasts from LDS.  Where the launch holds few waves, nothing hides
@@ -905,9 +906,10 @@ __device__ __forceinline__ GradTerm grad_term(int l) {
 // entry is kept by the lane of the entry's position in its 64-entry chunk,
 // added to the workgroup's once per chunk and to hits[g] at the flush.
 //
-// VALU issue bounds this walk (one wave64 instruction per CU and cycle), and
-// the sums over the wave's 64 pixels were half of it.  They are a
-// contraction: the columns A, B, C' of dL/dw and the low-pass centre are the
+// On many tiles VALU issue takes most of this walk (independent FP32
+// instructions issue at 1.6 wave64 ones per CU and cycle with vector operands,
+// 0.9 with a scalar one), and the sums over the wave's 64 pixels were a third
+// of its instructions.  They are a contraction: the columns A, B, C' of dL/dw and the low-pass centre are the
 // sums of {dw0, dw1, dw2, f2} times {dx, dy, 1}, and dx and dy depend on the
 // pixel's column and row alone, so only those four values and four plain sums
 // (opacity, colour) go through the reduction, not 15 products.

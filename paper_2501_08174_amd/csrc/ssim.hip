@@ -21,9 +21,11 @@
 // rows per row instead of 1.6, and the tile's loads are all issued before the
 // first is used (one by one, their latency was half of the kernels' time).
 // 16 views, 14.6 Mpx: forward 785 -> 530 us, backward 401 -> 313 us, totals
-// (a block per view) 177 -> 13 us.  The forward is bound by VALU issue (0.40 ms
-// of it: taps, halo, one division a pixel), the backward by the traffic of the
-// three gradient maps (36 bytes a pixel written and read).
+// (a block per view) 177 -> 13 us.  The forward is bound by VALU issue (245M
+// wave instructions, most with the tap in a scalar register; such issue at 0.9
+// per CU and cycle: 0.44 ms), the backward by the traffic of the
+// three gradient maps (36 bytes a pixel written and read) and its latency
+// between two barriers (105M, 0.19 ms).
 // Per-tile sums are reduced per view in a fixed order.
 #include <cmath>
 

@@ -909,10 +909,11 @@ __device__ __forceinline__ GradTerm grad_term(int l) {
 // On many tiles VALU issue takes most of this walk (independent FP32
 // instructions issue at 1.6 wave64 ones per CU and cycle with vector operands,
 // 0.9 with a scalar one), and the sums over the wave's 64 pixels were a third
-// of its instructions.  They are a contraction: the columns A, B, C' of dL/dw and the low-pass centre are the
-// sums of {dw0, dw1, dw2, f2} times {dx, dy, 1}, and dx and dy depend on the
-// pixel's column and row alone, so only those four values and four plain sums
-// (opacity, colour) go through the reduction, not 15 products.
+// of its instructions.  They are a contraction: the columns A, B, C' of dL/dw
+// and the low-pass centre are the sums of {dw0, dw1, dw2, f2} times
+// {dx, dy, 1}, and dx and dy depend on the pixel's column and row alone, so
+// only those four values and four plain sums (opacity, colour) go through the
+// reduction, not 15 products.
 template <int TW, int NT, int BATCH, bool GEO, bool SCALAR, bool HITS>
 __device__ __forceinline__ void bwd_tile(const TileCtx& t, float px, float py, int N, const float4* __restrict__ geom,
                                          const float4* __restrict__ app, const uint32_t* __restrict__ vals,

@@ -17,8 +17,6 @@
 // stable LSD radix sort.
 // Every count lives in device memory, so the sequence needs no host
 // synchronisation and can be captured into a HIP graph.
-#include <algorithm>
-
 #include "common.h"
 #include "launch.h"
 
@@ -629,8 +627,7 @@ k_inst_offsets(const uint32_t* __restrict__ counters, int G, const uint32_t* __r
 // instances take small blocks (1.1M instances: 23 us with 4096, 8 us with
 // 1024; 5.6M: 36 and 32); beyond, the chip is full and larger ones read fewer pairs twice.
 constexpr int kEmitSmall = 1024, kEmitLarge = 4096;
-constexpr uint64_t kEmitSmallCap = 16u << 20;
-inline int emit_per_block(uint64_t cap) { return cap <= kEmitSmallCap ? kEmitSmall : kEmitLarge; }
+inline int emit_per_block(uint64_t cap) { return cap <= (16u << 20) ? kEmitSmall : kEmitLarge; }
 
 // First visible pair of every emission block: the last pair whose first
 // instance is at or before the block's first output position (one thread per
@@ -798,24 +795,10 @@ int grid_pairs(uint64_t VN) { return blocks_for(VN, 1024); }
 struct RadixGrid {
     int ipt, blocks;
 };
-constexpr uint64_t kRadixFew = 1u << 18, kRadixSome = 1u << 21;
 RadixGrid radix_grid(uint64_t elems, int many) {
-    if (elems <= kRadixFew) return {4, blocks_for(elems, kNT * 4)};
-    if (elems <= kRadixSome) return {8, blocks_for(elems, kNT * 8)};
+    if (elems <= (1u << 18)) return {4, blocks_for(elems, kNT * 4)};
+    if (elems <= (1u << 21)) return {8, blocks_for(elems, kNT * 8)};
     return {many, blocks_for(elems, kTile)};
-}
-
-// Sizes of the workspaces: the most blocks of any pass over up to so many
-// elements.  The block sizes grow at the limits above, so the blocks fall
-// there; a workspace that holds the largest case has to hold the smaller ones.
-int radix_blocks_upto(uint64_t elems) {
-    int most = radix_grid(elems, 16).blocks;
-    for (const uint64_t limit : {kRadixFew, kRadixSome})
-        if (limit < elems) most = std::max(most, radix_grid(limit, 16).blocks);
-    return most;
-}
-uint64_t emit_blocks_upto(uint64_t cap) {
-    return std::max((std::min(cap, kEmitSmallCap) + kEmitSmall - 1) / kEmitSmall, (cap + kEmitLarge - 1) / kEmitLarge);
 }
 
 void radix_pass(const RadixGrid& g, const uint32_t* sk, const uint32_t* sv, const uint32_t* count, int shift, int bits,
@@ -848,13 +831,18 @@ BinWs carve(void* base, uint64_t VN, uint64_t cap) {
     w.ik0 = (uint32_t*)take(cap * 4); w.iv0 = (uint32_t*)take(cap * 4);
     w.ik1 = (uint32_t*)take(cap * 4); w.iv1 = (uint32_t*)take(cap * 4);
     w.hist = (uint32_t*)take((uint64_t)kMaxRadix * kMaxRadixBlocks * 4);
+    // the emission runs between the two sorts: its starts lie in their
+    // histogram (no part of the size that falls where the blocks grow)
+    static_assert(kMaxRadix * kMaxRadixBlocks >= (int)((1ull << 32) / kEmitLarge) &&
+                      kMaxRadix * kMaxRadixBlocks >= (16 << 20) / kEmitSmall,
+                  "starts of every emission block");
+    w.estart = w.hist;
     w.tot = (uint32_t*)take(kMaxRadix * 4);
     w.vsum = (uint32_t*)take(kMaxRadixBlocks * 4);
     w.isum = (uint64_t*)take(kMaxRadixBlocks * 8);
     w.ioff = (uint64_t*)take(VN * 8);
     w.tts = (uint32_t*)take(VN * 4);
     w.rsort = (ushort4*)take(VN * 8);
-    w.estart = (uint32_t*)take(emit_blocks_upto(cap) * 4);
     w.itotal = (uint64_t*)take(8);
     w.bytes = off;
     return w;
@@ -1044,7 +1032,6 @@ struct OrderWs {
 };
 
 size_t order_ws_layout(int T, void* base, OrderWs* w) {
-    const uint64_t G = (uint64_t)radix_blocks_upto((uint64_t)T);
     uint64_t off = 0;
     auto take = [&](uint64_t bytes) -> uint32_t* {
         uint32_t* p = base ? (uint32_t*)((char*)base + off) : nullptr;
@@ -1055,7 +1042,12 @@ size_t order_ws_layout(int T, void* base, OrderWs* w) {
     w->v0 = take((uint64_t)T * 4);
     w->k1 = take((uint64_t)T * 4);
     w->v1 = take((uint64_t)T * 4);
-    w->hist = take((uint64_t)kMaxRadix * G * 4);
+    // one pass writes its values to the order, not to v1: the histogram, of a
+    // block per 1024 tiles or fewer, lies there (more tiles than one block
+    // sorts, launch_tile_order), and the size has no part that falls where the
+    // blocks grow
+    static_assert(kOrderBits <= kMaxDigitBits && kMaxRadix * 2 <= 1024, "one pass, histogram of at most half of v1");
+    w->hist = w->v1;
     w->tot = take(kMaxRadix * 4);
     w->count = take(4);
     return (size_t)off;
